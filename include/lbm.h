@@ -193,8 +193,8 @@ lbm_status lbm_set_friction_spectral(lbm_ctx *ctx, const lbm_spectral *sp,
  * (lambda may alias omega).  Both arrays are owned by the caller.
  * hip_stream: a hipStream_t (NULL = default stream); asynchronous, no
  * synchronisation, no allocation, no memset, so it may be captured.  The raw
- * quadrature sums live in a fixed device array of LBM_STATIC_MAX_NODES + 1
- * doubles (8 MiB) per GPU, held until the process ends and shared by every
+ * quadrature sums and its tables live in a fixed device array of
+ * LBM_STATIC_MAX_NODES + 1 doubles and 16 MiB (24 MiB) per GPU, held until the process ends and shared by every
  * call on that GPU: calls that overlap on one GPU (on different streams
  * without ordering) race.  n > LBM_STATIC_MAX_NODES or invalid spectral
  * parameters -> LBM_EINVAL; a failed launch -> LBM_EDEVICE. */

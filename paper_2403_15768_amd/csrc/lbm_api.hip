@@ -961,7 +961,9 @@ lbm_status lbm_set_friction_spectral(lbm_ctx* c, const lbm_spectral* sp, const d
   if (n)
     HIPCHK(c, hipMemcpyAsync(dl, omega, n * sizeof(double),
                              on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, lbm::launch_friction(spec_args(sp), dl, (int64_t)n, draw, dl, c->stream));
+  // the buffer the next step overwrites serves as scratch (>= 18 B per node)
+  HIPCHK(c, lbm::launch_friction(spec_args(sp), dl, (int64_t)n, draw, dl, c->pop[1 - c->cur],
+                                 (int64_t)c->pl.pop_bytes, c->stream));
   c->have_raw = true;
   return upload_wall_r(c, dl, (int64_t)n);
 }

@@ -48,8 +48,13 @@ hipError_t launch_moments(int q, int prec, const void* src, const StepArgs& a, b
 // memory, device pointer) receives the same if not null
 hipError_t launch_reduce_final(const double* partials, int64_t nblocks, double* out, int nx,
                                double mass0, hipStream_t st, double* out_host = nullptr);
+// the friction quadrature; scratch (device, at least 18 n bytes) holds the
+// tables of the piecewise sums, which take over from the node-by-node sums
+// at kQuadSharedNodes nodes (spectra whose omega sum does not depend on q) or
+// kQuadTableNodes (the others).  The result does not depend on its size.
+constexpr int64_t kQuadSharedNodes = 2560, kQuadTableNodes = 18432;
 hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, double* raw,
-                           double* lambda, hipStream_t st);
+                           double* lambda, void* scratch, int64_t scratch_bytes, hipStream_t st);
 hipError_t launch_set_step(int64_t* d, int64_t v, hipStream_t st);
 const void* add_step_kernel_ptr();  // k_add_step(int64_t* d, int64_t v)
 // storage-precision change (0 F64, 1 F32, 2 F16S) of `rows` x-lines of nx

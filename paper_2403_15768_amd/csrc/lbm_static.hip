@@ -1,11 +1,11 @@
 // lbm_static.hip -- the friction quadrature for callers that cannot allocate.
 //
 // lbm_friction_quadrature_static() runs the same kernels as
-// lbm_set_friction_spectral() (k_friction_raw / k_friction_full, then the
-// normalisation k_friction_lat) on caller-owned device arrays, with no
-// context and no device allocation: the raw quadrature sums, which the
-// normalisation needs and the context keeps in its arena, live in a
-// file-scope device array of fixed size instead.  Each GPU holds its own
+// lbm_set_friction_spectral() on caller-owned device arrays, with no context
+// and no device allocation: the raw quadrature sums, which the normalisation
+// needs, and the tables of the piecewise sums, both of which the context
+// keeps in its arena, live in a file-scope device array of fixed size
+// instead.  Each GPU holds its own
 // copy of that array until the process ends.  The host never passes the
 // array's name to a kernel (in host code it is a stand-in, not a device
 // address): the device address is looked up once per device with
@@ -18,8 +18,11 @@
 
 // raw sums of at most kStaticMaxNodes wall nodes plus the reference (8 MiB)
 constexpr size_t kStaticMaxNodes = LBM_STATIC_MAX_NODES;
+// and behind them the tables of the piecewise sums (16 MiB)
+constexpr size_t kRawDoubles = (kStaticMaxNodes + 1 + 31) / 32 * 32;
+constexpr size_t kTableDoubles = (size_t)2 << 20;
 
-static __device__ __align__(256) double scratch[kStaticMaxNodes + 1];
+static __device__ __align__(256) double scratch[kRawDoubles + kTableDoubles];
 
 namespace {
 
@@ -59,7 +62,9 @@ lbm_status lbm_friction_quadrature_static(const lbm_spectral* sp, const double* 
   // every raw sum the normalisation reads (k <= n) is written first by the
   // quadrature kernel on the same stream: nothing needs clearing
   const hipError_t e = lbm::launch_friction(lbm_host::spec_args(sp), omega, (int64_t)n, raw,
-                                            lambda, reinterpret_cast<hipStream_t>(hip_stream));
+                                            lambda, raw + kRawDoubles,
+                                            (int64_t)(kTableDoubles * sizeof(double)),
+                                            reinterpret_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 

@@ -1,0 +1,123 @@
+"""GPU: the friction quadrature from piecewise-polynomial omega sums (many
+wall nodes) against the oracle's term-by-term long double sums on sampled nodes."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2403_15768_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# positive terms, so the relative error of a sum is that of its terms and of
+# its additions: at most 1500 sequential additions of 1.1e-16, some 1e-13 at
+# the very worst (the interpolation error, below 1e-17, does not show)
+TOL = 2e-13
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2403_15768_amd import lbm as mod
+
+    mod.load()
+    return mod
+
+
+def spectra(nq, nw, coupling, v_l, disp, gamma_s=None):
+    sp = inputs.draw_spectral(inputs.rng_for("tube", 77), nq=nq, nw=nw)
+    sp.coupling, sp.v_l, sp.dispersion = coupling, v_l, disp
+    if gamma_s is not None:
+        sp.gamma_s = gamma_s
+    return sp
+
+
+def oracle_spectra(sp):
+    return oracle.Spectral(T=sp.T, omega0=sp.omega0, gamma_s=sp.gamma_s, omega_l=sp.omega_l,
+                           gamma_l=sp.gamma_l, a_l=sp.a_l, d=sp.d, nq=sp.nq, nw=sp.nw,
+                           lambda_target=sp.lambda_target, dispersion=sp.dispersion,
+                           coupling=sp.coupling, v_l=sp.v_l)
+
+
+def static(lbm, sp, om):
+    import torch
+
+    s = lbm.make_spectral(sp)
+    d = torch.tensor(om, dtype=torch.float64, device="cuda")
+    rc = lbm.load().lbm_friction_quadrature_static(
+        C.byref(s), C.c_void_p(d.data_ptr()), len(om), C.c_void_p(d.data_ptr()),
+        C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    return d.cpu().numpy()
+
+
+# (nx of a 16 x 16 duct with 60 wall columns, spectra, range of Omega / omega0):
+# the smallest node counts that take the tables (2560 shared, 18432 per q) and
+# fewer, a part of a group of 8 q, one omega, one Omega for every node,
+# and frequencies down to zero
+@pytest.mark.parametrize("nx,nq,nw,coupling,v_l,disp,lo,hi", [
+    (42, 64, 100, 0, 0.0, 1, 0.4, 1.6),
+    (43, 64, 100, 0, 0.0, 1, 0.4, 1.6),
+    (43, 19, 1500, 0, 0.0, 0, 0.4, 1.6),
+    (43, 5, 1, 0, 0.0, 1, 1.2, 1.2),
+    (43, 33, 64, 0, 0.0, 1, 0.0, 2.0),
+    (307, 33, 100, 1, 0.4, 1, 0.4, 1.6),
+    (308, 33, 100, 1, 0.4, 1, 0.4, 1.6),
+    (308, 256, 512, 1, 0.0, 1, 0.6, 1.4),
+    (308, 17, 700, 1, 0.3, 0, 1.3, 1.3),
+    (308, 16, 64, 0, 0.7, 1, 0.0, 2.0),
+])
+def test_piecewise_sums(lbm, nx, nq, nw, coupling, v_l, disp, lo, hi):
+    check(lbm, nx, spectra(nq, nw, coupling, v_l, disp), lo, hi, TOL)
+
+
+# spectra whose poles are so close to the axis that a table would be too long:
+# summed term by term inside the evaluation.  There a resonance magnifies the
+# roundings of P - w^2 (three of P, three of w^2, each 1.1e-16 relative) by
+# P / (gamma_s w) ~ s / gamma_s, s <= Omega_max sqrt(q_max d)
+@pytest.mark.parametrize("nx,nq,nw,coupling,v_l", [(43, 40, 600, 0, 0.0), (308, 18, 600, 1, 0.2)])
+def test_spectra_without_tables(lbm, nx, nq, nw, coupling, v_l):
+    sp = spectra(nq, nw, coupling, v_l, 1, gamma_s=0.002)
+    s_max = 1.5 * sp.omega0 * np.sqrt(10.0)
+    check(lbm, nx, sp, 0.5, 1.5, TOL + 6 * 1.1e-16 * s_max / sp.gamma_s)
+
+
+def check(lbm, nx, sp, lo, hi, tol):
+    print("piecewise sums", nx, sp, lo, hi, flush=True)
+    G = lbm.Channel(19, lbm.DUCT, nx, 16, 16, tau=0.7, precision="f16s")
+    n = G.wall_count
+    assert n == 60 * nx
+    om = sp.omega0 * np.random.default_rng(3).uniform(lo, hi, n)
+    om[0], om[-1] = sp.omega0 * lo, sp.omega0 * hi
+    G.set_friction_spectral(sp, om)
+    lam, raw = G.get_friction(raw=True)
+    pick = np.unique(np.r_[0, n - 1, np.random.default_rng(4).integers(0, n, 20)])
+    raw_o, lam_o = oracle.friction(oracle_spectra(sp), om[pick], kind="f80")
+    ok = raw_o > 0
+    assert np.array_equal(raw[pick][~ok], raw_o[~ok])
+    err = np.max(np.abs(raw[pick][ok] / raw_o[ok] - 1))
+    print(f"  {n} nodes, max relative error {err:.2e}", flush=True)
+    assert err < tol
+    assert np.max(np.abs(lam[pick][ok] / lam_o[ok] - 1)) < 2 * tol
+    # the static entry point, whose scratch holds more tables at once: the same bits
+    assert np.array_equal(static(lbm, sp, om), lam)
+
+
+@pytest.mark.parametrize("coupling", [0, 1])
+def test_a_bad_frequency_stays_its_own(lbm, coupling):
+    print("bad frequency", coupling, flush=True)
+    sp = spectra(32, 64, coupling, 0.0, 1)
+    om = sp.omega0 * np.random.default_rng(5).uniform(0.5, 1.5, 20000)
+    clean = static(lbm, sp, om)
+    bad = om.copy()
+    bad[[7, 4000]] = np.nan, np.inf
+    got = static(lbm, sp, bad)
+    assert np.all(np.isnan(got[[7, 4000]]))
+    rest = np.ones(len(om), bool)
+    rest[[7, 4000]] = False
+    # (the two nodes' own frequencies may have set the ends of the range)
+    assert np.max(np.abs(got[rest] / clean[rest] - 1)) < 2 * TOL
