@@ -109,6 +109,44 @@ lbm_status validate(const lbm_params* p, std::string* err) {
   return LBM_OK;
 }
 
+// Tile and number of steps of the D2Q9 many-step kernel with at most kmax
+// steps per launch, by a model of its time fitted to measured ones: a launch
+// with its loads and stores 2.4 us, a step's latency 0.6 us and 0.3 us more
+// per wave on a SIMD; against a launch per step (k = 0 where that is faster).
+// The model's choice was within 4 % of the best of all tiles and k for most of
+// 12 sizes from 16 x 8 to 1024 x 128 (at worst 29 %, 512 x 300), and faster
+// than a launch per step at all of them.
+lbm::RunArgs plan_run(int nx, int ny, bool padded, int kmax) {
+  lbm::RunArgs best{};
+  double t_best = std::max(2.6, 2.4 + (double)nx * ny * 1e-5);
+  auto consider = [&](int tx, int ty, int k, bool whole) {
+    const int rx = whole ? nx : tx + 2 * k;
+    const int64_t n = (int64_t)rx * std::min(ny, ty + 2 * k);
+    const int cells = n <= lbm::run_lanes() ? 1 : 2;
+    if (n > 2 * lbm::run_lanes() || (cells == 2 && padded)) return;
+    const int xt = (nx + tx - 1) / tx;
+    const int64_t blocks = (int64_t)xt * ((ny + ty - 1) / ty);
+    if (blocks > 256) return;  // more than one round
+    double t = 2.4;
+    for (int j = 0; j < k; j++) {
+      const double rows = std::min(ny, ty + 2 * (k - 1 - j));
+      t += 0.6 + 0.3 * (whole ? rx : rx - 2 * (j + 1)) * rows / 256.0;
+    }
+    if (t >= t_best * k) return;
+    t_best = t / k;
+    best = lbm::RunArgs{(int)blocks, (int)((n + cells - 1) / cells + 63) / 64 * 64, xt, tx, ty, rx,
+                        k, whole ? 1 : 0, cells, nullptr};
+  };
+  for (int k = 2; k <= kmax; k *= 2)
+    for (int ty = ny;; ty = (ty + 1) / 2) {  // all rows, or halves of them, ...
+      consider(nx, ty, k, true);
+      for (int tx = 1; tx + 2 * k <= nx; tx *= 2)  // a halo wraps around at most once
+        consider(tx, ty, k, false);
+      if (ty <= 4) break;
+    }
+  return best;
+}
+
 lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
   lbm_status s = validate(p, err);
   if (s != LBM_OK) return s;
@@ -405,6 +443,12 @@ lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
     }
   }
 
+  if (pl.Q == 9 && !pl.masked) {
+    // powers of two: an even number of launches in a graph, which brings the
+    // buffers' parity back
+    pl.run = plan_run(pl.nx, pl.ny, pl.nxp > pl.nx, kGraphSteps / 2);
+  }
+
   size_t off = 0;
   pl.pop_bytes = (size_t)pl.ncolbox * pl.sC * pl.ssize;
   auto take = [&](size_t bytes) {
@@ -434,6 +478,7 @@ lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
   // open ends: per population buffer, [side][column][4] records of the end nodes
   pl.off_bmom = take((size_t)2 * 2 * pl.ncolbox * 4 * sizeof(double));
   pl.off_ptab = take(pl.ptab.size());
+  pl.off_cols = take(pl.run.k ? pl.colinfo.size() * sizeof(ColInfo) : 0);
   pl.total = off;
   return LBM_OK;
 }
@@ -582,8 +627,78 @@ lbm_status lbm_host::launch_one_step(lbm_ctx* c, bool check) {
 
 namespace {
 
+// How many plain steps one launch takes (1: the step kernel).
+int steps_per_launch(const lbm_ctx* c) {
+  if (c->elec || c->args.open || c->args.th_mode != 0) return 1;
+  return c->pl.run.k ? c->pl.run.k : 1;
+}
+
+lbm::RunArgs run_args(const lbm_ctx* c) {
+  lbm::RunArgs r = c->pl.run;
+  r.cols = c->at<ColInfo>(c->pl.off_cols);
+  return r;
+}
+
+lbm_status launch_steps(lbm_ctx* c, int k) {  // 2 <= k <= steps_per_launch
+  StepArgs a = c->args;
+  a.step_off = c->step;
+  lbm::RunArgs r = run_args(c);
+  if (!r.whole) r.rx = r.tx + 2 * k;
+  r.k = k;
+  HIPCHK(c, lbm::launch_step_run(c->pl.prec, c->pop[c->cur], c->pop[1 - c->cur], a, r, c->stream));
+  c->cur = 1 - c->cur;
+  c->step += k;
+  return LBM_OK;
+}
+
+// A graph of kGraphSteps / k chained k-step kernels from buffer `parity`.
+lbm_status build_steps_graph(lbm_ctx* c, int parity, int k) {
+  hipGraph_t g = nullptr;
+  HIPCHK(c, hipGraphCreate(&g, 0));
+  const void* pops[2] = {c->pop[parity], c->pop[1 - parity]};
+  int64_t* dstep = c->at<int64_t>(c->pl.off_step);
+  lbm::RunArgs ra = run_args(c);
+  const int n = kGraphSteps / k;  // even
+  hipGraphNode_t prev = nullptr;
+  hipError_t e = hipSuccess;
+  for (int m = 0; m <= n && e == hipSuccess; m++) {
+    StepArgs a = c->args;
+    a.dstep = dstep;
+    a.step_off = (int64_t)m * k;
+    int64_t inc = kGraphSteps;
+    void* sargs[4] = {(void*)&pops[m & 1], (void*)&pops[1 - (m & 1)], (void*)&a, (void*)&ra};
+    void* iargs[2] = {(void*)&dstep, (void*)&inc};
+    hipKernelNodeParams kp{};
+    kp.kernelParams = sargs;
+    if (m == n) {  // a last node advances the step base
+      kp.func = const_cast<void*>(lbm::add_step_kernel_ptr());
+      kp.gridDim = dim3(1);
+      kp.blockDim = dim3(64);
+      kp.kernelParams = iargs;
+    } else {
+      kp.func = const_cast<void*>(lbm::run_kernel_ptr(c->pl.prec, ra.cells));
+      kp.gridDim = dim3((unsigned)ra.blocks);
+      kp.blockDim = dim3((unsigned)ra.lanes);
+    }
+    hipGraphNode_t node = nullptr;
+    e = hipGraphAddKernelNode(&node, g, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
+    prev = node;
+  }
+  hipGraphExec_t ex = nullptr;
+  if (e == hipSuccess) e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
+  if (e != hipSuccess) {
+    (void)hipGraphDestroy(g);
+    return c->hip(e, "graph of several steps per launch");
+  }
+  c->graph[parity] = g;
+  c->gexec[parity] = ex;
+  return LBM_OK;
+}
+
 // A graph of kGraphSteps chained step kernels starting from buffer `parity`.
 lbm_status build_graph(lbm_ctx* c, int parity) {
+  const int per = steps_per_launch(c);
+  if (per > 1) return build_steps_graph(c, parity, per);
   hipGraph_t g = nullptr;
   HIPCHK(c, hipGraphCreate(&g, 0));
   const void* fn = lbm::step_kernel_ptr(c->pl.Q, c->pl.prec, c->pl.bouz, c->args.th_mode,
@@ -693,6 +808,12 @@ lbm_status do_steps(lbm_ctx* c, int64_t n) {
     c->step += kGraphSteps;  // even count: buffer parity unchanged
     c->dstep_value += kGraphSteps;
     n -= kGraphSteps;
+  }
+  for (const int per = steps_per_launch(c); n >= 2 && per > 1;) {
+    const int k = (int)std::min<int64_t>(n, per);
+    lbm_status s = launch_steps(c, k);
+    if (s != LBM_OK) return s;
+    n -= k;
   }
   for (; n > 0; n--) {
     lbm_status s = launch_one_step(c);
@@ -807,6 +928,9 @@ lbm_status lbm_create(const lbm_params* p, void* arena, size_t arena_bytes, void
       break;
     if (!pl.shellof.empty() &&
         (st = upload(c, pl.off_shellof, pl.shellof.data(), pl.shellof.size() * sizeof(int32_t))) != LBM_OK)
+      break;
+    if (pl.run.k &&
+        (st = upload(c, pl.off_cols, pl.colinfo.data(), pl.colinfo.size() * sizeof(ColInfo))) != LBM_OK)
       break;
     if (pl.masked &&
         ((st = upload(c, pl.off_cellw, pl.cellw.data(), pl.cellw.size() * sizeof(int32_t))) != LBM_OK ||

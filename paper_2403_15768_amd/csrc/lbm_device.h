@@ -1008,10 +1008,11 @@ __device__ __forceinline__ void store_pop(LBM_GLOBAL S* p, S v) {
     *p = v;
 }
 
-template <class L, typename M, typename S, int TH = 0, bool REC = false, bool NT = false>
-__device__ __forceinline__ void collide_store(const M* df, const StepArgs& a, LBM_GLOBAL S* out_col,
-                                              unsigned x, uint32_t cell, int64_t step,
-                                              const M* xi = nullptr, M* rec = nullptr) {
+// The update itself: every new population i goes to put(i, value) as soon as
+// it is computed.
+template <class L, typename M, typename S, int TH = 0, bool REC = false, class Put>
+__device__ __forceinline__ void collide(const M* df, const StepArgs& a, uint32_t cell, int64_t step,
+                                        const M* xi, M* rec, Put put) {
   constexpr bool THERM = TH != 0;
   M drho = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
@@ -1049,7 +1050,7 @@ __device__ __forceinline__ void collide_store(const M* df, const StepArgs& a, LB
     M v = keep * df[0] + static_cast<M>(L::w[0]) * C0;
     if constexpr (THERM) v += xi[0] * sc;
     const S e = Store<S, M>::enc(v, w0);
-    store_pop<NT>(at(sbase(out_col + L::row[0] * a.sI), x), e);
+    put(0, e);
     if constexpr (REC) {
       rec[0] = dec<S, M>(e);
       rec[1] = rec[2] = rec[3] = M(0);
@@ -1074,8 +1075,8 @@ __device__ __forceinline__ void collide_store(const M* df, const StepArgs& a, LB
     const uint32_t word = Store<S, M>::kRandom ? rb.next() : 0u;
     S ei, eo;
     Store<S, M>::enc2(vi, vo, word, &ei, &eo);
-    store_pop<NT>(at(sbase(out_col + L::row[i] * a.sI), x), ei);
-    store_pop<NT>(at(sbase(out_col + L::row[o] * a.sI), x), eo);
+    put(i, ei);
+    put(o, eo);
     if constexpr (REC) {  // c_o = -c_i
       const M di = dec<S, M>(ei), dd = di - dec<S, M>(eo);
       rec[0] += di + dec<S, M>(eo);
@@ -1084,6 +1085,16 @@ __device__ __forceinline__ void collide_store(const M* df, const StepArgs& a, LB
       if (L::cz[i]) rec[3] += L::cz[i] > 0 ? dd : -dd;
     }
   }
+}
+
+// ... stored to the column at out_col, element x of each of its x-lines
+template <class L, typename M, typename S, int TH = 0, bool REC = false, bool NT = false>
+__device__ __forceinline__ void collide_store(const M* df, const StepArgs& a, LBM_GLOBAL S* out_col,
+                                              unsigned x, uint32_t cell, int64_t step,
+                                              const M* xi = nullptr, M* rec = nullptr) {
+  collide<L, M, S, TH, REC>(df, a, cell, step, xi, rec, [&](int i, S e) {
+    store_pop<NT>(at(sbase(out_col + L::row[i] * a.sI), x), e);
+  });
 }
 
 }  // namespace lbm

@@ -29,6 +29,18 @@ hipError_t launch_step(int q, int prec, const void* src, void* dst, const StepAr
 // order); planar or tube walls without noise, sheets, mask or open ends
 hipError_t launch_step_checked(int q, int prec, const void* src, void* dst, const StepArgs& a,
                                bool bouz, hipStream_t st);
+// k steps per launch of a D2Q9 slab without noise, sheets or open ends: tiles of tx x ty cells, in LDS
+// with k cells on every side (rx = tx + 2 k), or of whole x-lines (rx = tx =
+// nx); cells (1 or 2) per lane
+struct RunArgs {
+  int blocks, lanes;
+  int xtiles, tx, ty, rx, k, whole, cells;
+  const ColInfo* cols;
+};
+int run_lanes();  // most lanes of a workgroup
+hipError_t launch_step_run(int prec, const void* src, void* dst, const StepArgs& a,
+                           const RunArgs& ra, hipStream_t st);
+const void* run_kernel_ptr(int prec, int cells);  // (src, dst, StepArgs, RunArgs)
 const void* step_kernel_ptr(int q, int prec, bool bouz, int th_mode, bool elec,
                             bool masked, bool open, bool nt);
 // one electron step from the water state g (step n): e_src -> e_dst, u_e of

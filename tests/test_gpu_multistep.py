@@ -1,0 +1,73 @@
+"""GPU: several steps per launch against single steps, bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2403_15768_amd import lbm as mod
+
+    mod.load()
+    return mod
+
+
+def channel(lbm, geo, nx, ny, nz, precision, utop=0.0):
+    q = 9 if geo == "plane" else 19
+    kw = dict(tau=0.73, force=(1e-5, 2e-6, 0.0 if q == 9 else -1e-6), precision=precision)
+    ch = lbm.Channel(q, lbm.SLAB, nx, ny, nz, wall_velocity_top=utop, **kw)
+    lam = np.random.default_rng(nx + ny).uniform(0.0, 0.3, ch.wall_count)
+    lam[:: 7] = np.inf
+    ch.set_friction(lam)
+    return ch
+
+
+# D2Q9: whole channels in one workgroup, tiles with halos, padded and ragged
+# lines, one and two rows, a row count that leaves the kernel no room, a
+# channel of more tiles than it takes, a moving wall
+@pytest.mark.parametrize("nx,ny,utop", [
+    (1, 5, 0.0), (5, 1, 0.0), (7, 2, 0.0), (16, 8, 0.0), (64, 30, 0.0), (64, 30, 1e-3),
+    (130, 3, 0.0), (131, 40, 0.0), (200, 14, 0.0), (500, 128, 0.0), (257, 77, 1e-3),
+    (40, 700, 0.0), (3000, 20, 0.0), (20000, 9, 0.0),
+])
+@pytest.mark.parametrize("precision", ["f64", "f32", "f16s"])
+def test_plane_runs_equal_single_steps(lbm, nx, ny, utop, precision):
+    print("plane", nx, ny, utop, precision, flush=True)
+    compare(lbm, "plane", nx, ny, 1, precision, utop)
+
+
+def compare(lbm, geo, nx, ny, nz, precision, utop):
+    A, B = (channel(lbm, geo, nx, ny, nz, precision, utop) for _ in range(2))
+    # an odd start, plain launches, a graph, a rest
+    for n in (1, 7, 64 + 64 + 5):
+        A.step(n)
+        for _ in range(n):
+            B.step(1)
+        sa, sb = A.get_state(), B.get_state()
+        assert sa[1] == sb[1]
+        assert np.array_equal(np.asarray(sa[0]), np.asarray(sb[0])), n
+    assert A.flux() == B.flux() and np.isfinite(A.flux()) and A.flux() != 0.0
+
+
+def test_runs_start_and_stop_with_the_options(lbm):
+    # a channel whose options change between runs: noise on and off, graphs
+    # of both kinds
+    print("options", flush=True)
+    for geo, nx, ny, nz in (("slab", 40, 12, 10), ("plane", 50, 20, 1)):
+        options(lbm, geo, nx, ny, nz)
+
+
+def options(lbm, geo, nx, ny, nz):
+    A, B = (channel(lbm, geo, nx, ny, nz, "f32") for _ in range(2))
+    for kT in (0.0, 1e-6, 0.0):
+        A.set_thermal(kT, 1, 3)
+        B.set_thermal(kT, 1, 3)
+        A.step(131)
+        for _ in range(131):
+            B.step(1)
+        assert np.array_equal(np.asarray(A.get_state()[0]), np.asarray(B.get_state()[0])), kT
