@@ -147,6 +147,52 @@ lbm::RunArgs plan_run(int nx, int ny, bool padded, int kmax) {
   return best;
 }
 
+// Boxes of the D3Q19 two-step kernel, by a model of its time fitted to
+// measured ones (96 boxes of 11 channels, most within 15 %): a launch with its
+// loads and stores, the first step by the cells of the box and its
+// surroundings, and the second one.  None where a launch per step is not
+// slower by a sixth at least.
+void plan_box(const std::vector<unsigned char>& fluid, Plan* P) {
+  Plan& pl = *P;
+  // byte offsets are formed in 32 bits; the kernel writes no padding
+  if (pl.ncolbox * pl.sC * (int64_t)pl.ssize >= ((int64_t)1 << 32) || pl.nxp != pl.nx) return;
+  const bool f64 = pl.prec == LBM_F64, f32 = pl.prec == LBM_F32;
+  const double tube = pl.bouz ? 1.5 : 0.0;  // interpolated walls
+  const double launch = tube + (f64 ? 7.0 : (f32 ? 6.0 : 6.2));
+  const double first = f64 ? 0.004 : (f32 ? 0.0045 : 0.0035);
+  double t_best = 2.0 * 0.86 * (tube + (f64 ? 4.6 : (f32 ? 5.8 : 7.4)) +
+                                pl.nfluid * (f64 ? 3.5e-5 : (f32 ? 2.2e-5 : 2e-5)));
+  const int most = f64 ? 1024 : 2048;  // cells of a box in LDS
+  auto boxes = [&](int ty, int tz) {  // those that hold fluid
+    std::vector<lbm::BoxTile> out;
+    for (int z0 = 0; z0 < pl.nz; z0 += tz)
+      for (int y0 = 0; y0 < pl.ny; y0 += ty) {
+        const lbm::BoxTile b{y0, std::min(y0 + ty, pl.ny), z0, std::min(z0 + tz, pl.nz)};
+        bool any = !pl.bouz;
+        for (int z = b.z0; z < b.z1 && !any; z++)
+          for (int y = b.y0; y < b.y1 && !any; y++) any = fluid[y + (int64_t)pl.ny * z] != 0;
+        if (any) out.push_back(b);
+      }
+    return out;
+  };
+  for (int tz = 1; tz <= std::min(pl.nz, 16); tz++)
+    for (int ty = 1; ty <= std::min(pl.ny, 16); ty++) {
+      const int n = pl.nx * std::min(ty + 2, pl.ny) * (tz + 2);
+      if (n > most) break;
+      const double t = launch + first * n + 0.002 * pl.nx * ty * tz;
+      const int64_t all = (int64_t)((pl.ny + ty - 1) / ty) * ((pl.nz + tz - 1) / tz);
+      // at most one round of workgroups; of a tube's boxes, half may be empty
+      if (t >= t_best || all > (pl.bouz ? 512 : 256)) continue;
+      std::vector<lbm::BoxTile> tiles = boxes(ty, tz);
+      if (tiles.size() > 256) continue;
+      t_best = t;
+      pl.tiles = std::move(tiles);
+      const int c = n > 1024 ? 2 : 1;
+      pl.box = lbm::BoxArgs{(int)pl.tiles.size(), ((n + c - 1) / c + 63) / 64 * 64, c, nullptr,
+                            nullptr};
+    }
+}
+
 lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
   lbm_status s = validate(p, err);
   if (s != LBM_OK) return s;
@@ -443,6 +489,7 @@ lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
     }
   }
 
+  if (pl.Q == 19 && !pl.masked) plan_box(fluid, P);
   if (pl.Q == 9 && !pl.masked) {
     // powers of two: an even number of launches in a graph, which brings the
     // buffers' parity back
@@ -478,7 +525,8 @@ lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
   // open ends: per population buffer, [side][column][4] records of the end nodes
   pl.off_bmom = take((size_t)2 * 2 * pl.ncolbox * 4 * sizeof(double));
   pl.off_ptab = take(pl.ptab.size());
-  pl.off_cols = take(pl.run.k ? pl.colinfo.size() * sizeof(ColInfo) : 0);
+  pl.off_cols = take(pl.run.k || pl.box.blocks ? pl.colinfo.size() * sizeof(ColInfo) : 0);
+  pl.off_tiles = take(pl.tiles.size() * sizeof(lbm::BoxTile));
   pl.total = off;
   return LBM_OK;
 }
@@ -630,9 +678,15 @@ namespace {
 // How many plain steps one launch takes (1: the step kernel).
 int steps_per_launch(const lbm_ctx* c) {
   if (c->elec || c->args.open || c->args.th_mode != 0) return 1;
-  return c->pl.run.k ? c->pl.run.k : 1;
+  return c->pl.run.k ? c->pl.run.k : (c->pl.box.blocks ? 2 : 1);
 }
 
+lbm::BoxArgs box_args(const lbm_ctx* c) {
+  lbm::BoxArgs b = c->pl.box;
+  b.tiles = c->at<lbm::BoxTile>(c->pl.off_tiles);
+  b.cols = c->at<ColInfo>(c->pl.off_cols);
+  return b;
+}
 lbm::RunArgs run_args(const lbm_ctx* c) {
   lbm::RunArgs r = c->pl.run;
   r.cols = c->at<ColInfo>(c->pl.off_cols);
@@ -642,10 +696,15 @@ lbm::RunArgs run_args(const lbm_ctx* c) {
 lbm_status launch_steps(lbm_ctx* c, int k) {  // 2 <= k <= steps_per_launch
   StepArgs a = c->args;
   a.step_off = c->step;
-  lbm::RunArgs r = run_args(c);
-  if (!r.whole) r.rx = r.tx + 2 * k;
-  r.k = k;
-  HIPCHK(c, lbm::launch_step_run(c->pl.prec, c->pop[c->cur], c->pop[1 - c->cur], a, r, c->stream));
+  if (c->pl.run.k) {
+    lbm::RunArgs r = run_args(c);
+    if (!r.whole) r.rx = r.tx + 2 * k;
+    r.k = k;
+    HIPCHK(c, lbm::launch_step_run(c->pl.prec, c->pop[c->cur], c->pop[1 - c->cur], a, r, c->stream));
+  } else {
+    HIPCHK(c, lbm::launch_step_box(c->pl.prec, c->pop[c->cur], c->pop[1 - c->cur], a, box_args(c),
+                                   c->pl.bouz, c->stream));
+  }
   c->cur = 1 - c->cur;
   c->step += k;
   return LBM_OK;
@@ -657,6 +716,7 @@ lbm_status build_steps_graph(lbm_ctx* c, int parity, int k) {
   HIPCHK(c, hipGraphCreate(&g, 0));
   const void* pops[2] = {c->pop[parity], c->pop[1 - parity]};
   int64_t* dstep = c->at<int64_t>(c->pl.off_step);
+  lbm::BoxArgs ba = box_args(c);
   lbm::RunArgs ra = run_args(c);
   const int n = kGraphSteps / k;  // even
   hipGraphNode_t prev = nullptr;
@@ -666,7 +726,8 @@ lbm_status build_steps_graph(lbm_ctx* c, int parity, int k) {
     a.dstep = dstep;
     a.step_off = (int64_t)m * k;
     int64_t inc = kGraphSteps;
-    void* sargs[4] = {(void*)&pops[m & 1], (void*)&pops[1 - (m & 1)], (void*)&a, (void*)&ra};
+    void* sargs[4] = {(void*)&pops[m & 1], (void*)&pops[1 - (m & 1)], (void*)&a,
+                      ra.k ? (void*)&ra : (void*)&ba};
     void* iargs[2] = {(void*)&dstep, (void*)&inc};
     hipKernelNodeParams kp{};
     kp.kernelParams = sargs;
@@ -675,10 +736,14 @@ lbm_status build_steps_graph(lbm_ctx* c, int parity, int k) {
       kp.gridDim = dim3(1);
       kp.blockDim = dim3(64);
       kp.kernelParams = iargs;
-    } else {
+    } else if (ra.k) {
       kp.func = const_cast<void*>(lbm::run_kernel_ptr(c->pl.prec, ra.cells));
       kp.gridDim = dim3((unsigned)ra.blocks);
       kp.blockDim = dim3((unsigned)ra.lanes);
+    } else {
+      kp.func = const_cast<void*>(lbm::box_kernel_ptr(c->pl.prec, c->pl.bouz, ba.cells));
+      kp.gridDim = dim3((unsigned)ba.blocks);
+      kp.blockDim = dim3((unsigned)ba.lanes);
     }
     hipGraphNode_t node = nullptr;
     e = hipGraphAddKernelNode(&node, g, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
@@ -929,7 +994,10 @@ lbm_status lbm_create(const lbm_params* p, void* arena, size_t arena_bytes, void
     if (!pl.shellof.empty() &&
         (st = upload(c, pl.off_shellof, pl.shellof.data(), pl.shellof.size() * sizeof(int32_t))) != LBM_OK)
       break;
-    if (pl.run.k &&
+    if (pl.box.blocks &&
+        (st = upload(c, pl.off_tiles, pl.tiles.data(), pl.tiles.size() * sizeof(lbm::BoxTile))) != LBM_OK)
+      break;
+    if ((pl.run.k || pl.box.blocks) &&
         (st = upload(c, pl.off_cols, pl.colinfo.data(), pl.colinfo.size() * sizeof(ColInfo))) != LBM_OK)
       break;
     if (pl.masked &&

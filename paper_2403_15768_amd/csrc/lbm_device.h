@@ -170,6 +170,12 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
 // ------------------------------------------------------------------ electron lines
 // Electron shells (the solid columns next to the water, one line along x
 // each, D1Q3): slab and duct y = -1 and y = ny (by z), then for a duct

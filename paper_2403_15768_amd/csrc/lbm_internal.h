@@ -52,7 +52,9 @@ struct Plan {
   std::vector<int32_t> rowx;  // per wall row: count, then the x of its points ([y][nxp + 1])
   size_t off_cellw = 0, off_ptab = 0, off_rowx = 0;
   size_t off_bmom = 0;  // open ends: [side][column][4] moments of the end nodes
-  size_t off_cols = 0;
+  size_t off_cols = 0, off_tiles = 0;
+  lbm::BoxArgs box{};    // two steps per launch of a small D3Q19 channel (no blocks: none)
+  std::vector<lbm::BoxTile> tiles;
   lbm::RunArgs run{};  // k steps per launch of a D2Q9 slab (k = 0: none)
   int64_t nsheet = 0;               // electron shell nodes (nshell nx)
   // per shell: the wall column of the fluid column next to it (SLAB, DUCT);

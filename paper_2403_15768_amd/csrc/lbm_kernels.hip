@@ -83,12 +83,6 @@ __device__ __forceinline__ void step_cell(const S* __restrict__ src, S* __restri
     }
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // Per-block partial sums (s0, s1) over a block of the step or moments grid:
 // a fixed butterfly within each wave, then the waves in order (deterministic).
 __device__ __forceinline__ void block_partials(double s0, double s1, double* __restrict__ out) {
@@ -1081,3 +1075,6 @@ hipError_t launch_set_r(int prec, const double* lambda, int64_t n, void* r, int*
 }
 
 }  // namespace lbm
+
+#include "lbm_multistep.h"
+#include "lbm_quadrature.h"

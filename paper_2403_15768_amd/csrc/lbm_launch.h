@@ -29,6 +29,20 @@ hipError_t launch_step(int q, int prec, const void* src, void* dst, const StepAr
 // order); planar or tube walls without noise, sheets, mask or open ends
 hipError_t launch_step_checked(int q, int prec, const void* src, void* dst, const StepArgs& a,
                                bool bouz, hipStream_t st);
+// two steps per launch of a small D3Q19 channel (planar or tube walls without
+// noise, sheets, mask or open ends, populations of less than 4 GiB): boxes of
+// whole x-lines, one per tile; cells (1 or 2) per lane
+struct BoxTile {
+  int32_t y0, y1, z0, z1;
+};
+struct BoxArgs {
+  int blocks, lanes, cells;
+  const BoxTile* tiles;
+  const ColInfo* cols;  // per box column
+};
+hipError_t launch_step_box(int prec, const void* src, void* dst, const StepArgs& a,
+                           const BoxArgs& ba, bool bouz, hipStream_t st);
+const void* box_kernel_ptr(int prec, bool bouz, int cells);  // (src, dst, StepArgs, BoxArgs)
 // k steps per launch of a D2Q9 slab without noise, sheets or open ends: tiles of tx x ty cells, in LDS
 // with k cells on every side (rx = tx + 2 k), or of whole x-lines (rx = tx =
 // nx); cells (1 or 2) per lane

@@ -1,4 +1,5 @@
-// lbm_quadrature.hip -- the (q, omega) friction quadrature for gfx950.
+// lbm_quadrature.h -- the (q, omega) friction quadrature for gfx950 (part of
+// lbm_kernels.hip).
 //
 //  k_friction_raw   the sum node by node, omega table tiled through LDS, FP64
 //                   sums, wavefront + block reduction (few wall nodes)
@@ -8,6 +9,8 @@
 //                   the sum over omega as piecewise polynomials in
 //                   Omega sqrt(q d), evaluated per node and q (many wall nodes)
 //  k_friction_lat   normalisation lambda_k = lambda_target raw_k / raw_ref
+#pragma once
+
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -18,12 +21,6 @@
 #include "lbm_launch.h"
 
 namespace lbm {
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 // ------------------------------------------------------------ friction quadrature
 constexpr int kQuadThreads = 256;

@@ -2,6 +2,8 @@
 import numpy as np
 import pytest
 
+from paper_2403_15768_amd import inputs
+
 pytestmark = pytest.mark.gpu
 
 
@@ -20,7 +22,13 @@ def lbm():
 def channel(lbm, geo, nx, ny, nz, precision, utop=0.0):
     q = 9 if geo == "plane" else 19
     kw = dict(tau=0.73, force=(1e-5, 2e-6, 0.0 if q == 9 else -1e-6), precision=precision)
-    ch = lbm.Channel(q, lbm.SLAB, nx, ny, nz, wall_velocity_top=utop, **kw)
+    if geo == "tube":
+        _, _, cy, cz = inputs.tube_box(ny)
+        n = 2 * ny + 8
+        ch = lbm.Channel(q, lbm.TUBE, nx, n, n, tube_radius=float(ny), tube_cy=cy, tube_cz=cz, **kw)
+    else:
+        ch = lbm.Channel(q, lbm.DUCT if geo == "duct" else lbm.SLAB, nx, ny, nz,
+                         wall_velocity_top=utop, **kw)
     lam = np.random.default_rng(nx + ny).uniform(0.0, 0.3, ch.wall_count)
     lam[:: 7] = np.inf
     ch.set_friction(lam)
@@ -44,7 +52,7 @@ def test_plane_runs_equal_single_steps(lbm, nx, ny, utop, precision):
 def compare(lbm, geo, nx, ny, nz, precision, utop):
     A, B = (channel(lbm, geo, nx, ny, nz, precision, utop) for _ in range(2))
     # an odd start, plain launches, a graph, a rest
-    for n in (1, 7, 64 + 64 + 5):
+    for n in (1, 7, 64 + 64 + 5, 6):
         A.step(n)
         for _ in range(n):
             B.step(1)
@@ -58,7 +66,7 @@ def test_runs_start_and_stop_with_the_options(lbm):
     # a channel whose options change between runs: noise on and off, graphs
     # of both kinds
     print("options", flush=True)
-    for geo, nx, ny, nz in (("slab", 40, 12, 10), ("plane", 50, 20, 1)):
+    for geo, nx, ny, nz in (("duct", 40, 12, 10), ("plane", 50, 20, 1)):
         options(lbm, geo, nx, ny, nz)
 
 
@@ -71,3 +79,20 @@ def options(lbm, geo, nx, ny, nz):
         for _ in range(131):
             B.step(1)
         assert np.array_equal(np.asarray(A.get_state()[0]), np.asarray(B.get_state()[0])), kT
+
+
+# D3Q19 boxes: one and two cells per lane, box and channel edges, ragged boxes, columns without a box's full surroundings,
+# periodic z of one, two and more planes (a box reaching around), a moving wall,
+# tubes (interpolated walls, empty boxes), and channels too large for boxes
+@pytest.mark.parametrize("geo,nx,ny,nz", [
+    ("duct", 1, 2, 2), ("duct", 8, 3, 3), ("duct", 20, 17, 30), ("duct", 32, 32, 32),
+    ("duct", 16, 64, 64), ("duct", 32, 128, 64), ("duct", 33, 20, 45), ("duct", 64, 64, 32),
+    ("duct", 100, 12, 9), ("duct", 127, 5, 6), ("duct", 160, 9, 8), ("duct", 200, 9, 8),
+    ("slab", 40, 12, 1), ("slab", 24, 14, 2), ("slab", 16, 30, 21), ("slab", 64, 16, 5),
+    ("tube", 16, 8, 0), ("tube", 16, 11, 0), ("tube", 7, 3, 0), ("tube", 40, 16, 0),
+    ("tube", 128, 5, 0),
+])
+@pytest.mark.parametrize("precision", ["f64", "f32", "f16s"])
+def test_boxes_equal_single_steps(lbm, geo, nx, ny, nz, precision):
+    print("box", geo, nx, ny, nz, precision, flush=True)
+    compare(lbm, geo, nx, ny, nz, precision, 1e-3 if geo == "slab" and nx == 64 else 0.0)
