@@ -640,6 +640,15 @@ lbm_status lbm_host::ensure_end_records(lbm_ctx* c) {
   return LBM_OK;
 }
 
+namespace {
+// Whether the step kernel also steps the electron lines: those of a slab or
+// duct, whose shells belong to one fluid column each, where a workgroup holds
+// a whole x-line.
+bool lines_with_step(const lbm_ctx* c, const StepArgs& a) {
+  return c->elec && !c->pl.bouz && a.segs == 1;
+}
+}  // namespace
+
 lbm_status lbm_host::launch_one_step(lbm_ctx* c, bool check) {
   StepArgs a = c->args;
   a.step_off = c->step;  // plain launch: the step travels as an argument
@@ -655,6 +664,15 @@ lbm_status lbm_host::launch_one_step(lbm_ctx* c, bool check) {
   a = step_args(c);
   a.step_off = c->step;
   a.rev = c->cur;
+  if (lines_with_step(c, a)) {
+    HIPCHK(c, lbm::launch_step_lines(c->pl.Q, c->pl.prec, c->pop[c->cur], c->pop[1 - c->cur], a,
+                                     c->at<double>(c->pl.off_e[c->cur]),
+                                     c->at<double>(c->pl.off_e[1 - c->cur]),
+                                     c->at<double>(c->pl.off_ue), c->ea, c->stream));
+    c->cur = 1 - c->cur;
+    c->step++;
+    return LBM_OK;
+  }
   if (c->elec)  // the electrons of step n first: the water step reads their velocity
     HIPCHK(c, lbm::launch_electron_step(c->pl.Q, c->pl.prec, c->pop[c->cur],
                                         c->at<double>(c->pl.off_e[c->cur]),
@@ -769,7 +787,9 @@ lbm_status build_graph(lbm_ctx* c, int parity) {
   const void* fn = lbm::step_kernel_ptr(c->pl.Q, c->pl.prec, c->pl.bouz, c->args.th_mode,
                                         c->elec, c->pl.masked, c->args.open != 0,
                                         c->args.ntstore != 0);
-  const void* fe = c->elec ? lbm::electron_kernel_ptr(c->pl.Q, c->pl.prec) : nullptr;
+  const bool lines = lines_with_step(c, step_args(c));
+  if (lines) fn = lbm::lines_kernel_ptr(c->pl.Q, c->pl.prec, c->args.th_mode);
+  const void* fe = c->elec && !lines ? lbm::electron_kernel_ptr(c->pl.Q, c->pl.prec) : nullptr;
   double* bm[2] = {bmom_buf(c, parity), bmom_buf(c, 1 - parity)};
   const double* esrc[2] = {c->at<double>(c->pl.off_e[parity]), c->at<double>(c->pl.off_e[1 - parity])};
   double* edst[2] = {c->at<double>(c->pl.off_e[1 - parity]), c->at<double>(c->pl.off_e[parity])};
@@ -808,7 +828,9 @@ lbm_status build_graph(lbm_ctx* c, int parity) {
       args[k].bmom = bm[k & 1];
       args[k].bmom_out = bm[(k + 1) & 1];
     }
-    void* kargs[3] = {(void*)&srcs[k & 1], (void*)&dsts[k & 1], (void*)&args[k]};
+    // (the last four: the step that takes the lines with it)
+    void* kargs[7] = {(void*)&srcs[k & 1], (void*)&dsts[k & 1], (void*)&args[k],
+                      (void*)&esrc[k & 1], (void*)&edst[k & 1], (void*)&uep, (void*)&eargs};
     hipKernelNodeParams kp{};
     kp.func = const_cast<void*>(fn);
     kp.gridDim = dim3((unsigned)c->pl.slots.size(), (unsigned)base.segs);

@@ -3,6 +3,8 @@
 //  k_step           fused pull stream + Navier-slip wall + BGK/Guo collide,
 //                   one thread per fluid cell, ping-pong buffers; TH = 1, 2
 //                   adds thermal noise of that form (fluctuating LB)
+//  k_step_lines     k_step of a slab or duct with electron lines, their step
+//                   with it
 //  k_moments        moments of the current state (the populations the next
 //                   collision sees), per-block FP64 partials of the flux and
 //                   the mass deviation, optional dense field output
@@ -362,6 +364,38 @@ __device__ __forceinline__ void electron_node(const S* __restrict__ g,
     ed[i * n + s] = d[i] - om * (d[i] - eq) + src;
   }
   ue[s] = u;
+}
+
+// The water step of a slab or duct with electron lines, the lines' step with
+// it: each shell couples to one fluid column and that column's wall links pull
+// from its shells only, so the workgroup that updates a wall column (its whole
+// x-line) first steps the column's one or two shells, then the water, which
+// reads their new velocity.  One launch per step instead of two: the 256 x 128
+// x 64 duct in float, with phonons, 300 steps and the field 19.4 -> 17.9 ms.
+template <class L, typename S, typename M, int TH>
+__global__ void __launch_bounds__(512) k_step_lines(const S* __restrict__ src, S* __restrict__ dst,
+                                                    StepArgs a, const double* __restrict__ es,
+                                                    double* __restrict__ ed, double* ue,
+                                                    ElecArgs ea) {
+  int slot = blockIdx.x;
+  if (a.rev && slot >= a.nwallcols) slot = a.nactive - 1 - slot + a.nwallcols;
+  const int x = threadIdx.x;
+  if (slot < a.nwallcols) {
+    const int col = uniform(gbl(a.slots)[slot].col);
+    const int z = col / a.ny, y = col - z * a.ny;
+    if (x < a.nx) {
+      auto shell = [&](int64_t sh) {
+        electron_node<L, S, M>(src, es, ed, ue, ea, sh * a.nx + x);
+      };
+      if (y == 0) shell(z);
+      if (y == a.ny - 1) shell((int64_t)a.nz + z);
+      if (!a.slab && z == 0) shell(2LL * a.nz + y);
+      if (!a.slab && z == a.nz - 1) shell(2LL * a.nz + a.ny + y);
+    }
+    __syncthreads();  // the neighbours' velocities
+  }
+  if (x >= a.nxp) return;
+  step_cell<L, S, M, false, TH, true, false, false>(src, dst, a, slot, x, nullptr, nullptr);
 }
 
 template <class L, typename S, typename W>
@@ -952,6 +986,35 @@ hipError_t launch_step_checked(int q, int prec, const void* src, void* dst, cons
   if (prec == 0) return launch_step_checked_t<D3Q19, double, double>(src, dst, a, bouz, st);
   if (prec == 1) return launch_step_checked_t<D3Q19, float, double>(src, dst, a, bouz, st);
   return launch_step_checked_t<D3Q19, _Float16, float>(src, dst, a, bouz, st);
+}
+
+template <class L, typename S, typename M>
+static const void* lines_kernel_t(int th_mode) {
+  if (th_mode == 1) return reinterpret_cast<const void*>(&k_step_lines<L, S, M, 1>);
+  if (th_mode == 2) return reinterpret_cast<const void*>(&k_step_lines<L, S, M, 2>);
+  return reinterpret_cast<const void*>(&k_step_lines<L, S, M, 0>);
+}
+const void* lines_kernel_ptr(int q, int prec, int th_mode) {
+  if (q == 9) {
+    if (prec == 0) return lines_kernel_t<D2Q9, double, double>(th_mode);
+    if (prec == 1) return lines_kernel_t<D2Q9, float, double>(th_mode);
+    return lines_kernel_t<D2Q9, _Float16, float>(th_mode);
+  }
+  if (prec == 0) return lines_kernel_t<D3Q19, double, double>(th_mode);
+  if (prec == 1) return lines_kernel_t<D3Q19, float, double>(th_mode);
+  return lines_kernel_t<D3Q19, _Float16, float>(th_mode);
+}
+
+hipError_t launch_step_lines(int q, int prec, const void* src, void* dst, const StepArgs& a,
+                             const double* e_src, double* e_dst, double* ue, const ElecArgs& ea,
+                             hipStream_t st) {
+  if (a.segs != 1) return hipErrorInvalidValue;
+  StepArgs args = a;
+  ElecArgs eargs = ea;
+  void* kargs[7] = {(void*)&src,   (void*)&dst, (void*)&args, (void*)&e_src,
+                    (void*)&e_dst, (void*)&ue,  (void*)&eargs};
+  return hipLaunchKernel(lines_kernel_ptr(q, prec, a.th_mode), dim3((unsigned)a.nactive),
+                         dim3(a.bx), kargs, 0, st);
 }
 
 hipError_t launch_step(int q, int prec, const void* src, void* dst, const StepArgs& a, bool bouz,

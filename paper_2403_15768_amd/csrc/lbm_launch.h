@@ -62,6 +62,12 @@ const void* step_kernel_ptr(int q, int prec, bool bouz, int th_mode, bool elec,
 hipError_t launch_electron_step(int q, int prec, const void* g, const double* e_src,
                                 double* e_dst, double* ue, const ElecArgs& ea, hipStream_t st);
 const void* electron_kernel_ptr(int q, int prec);
+// both in one launch (slab and duct lines, one workgroup per x-line: a.segs = 1)
+hipError_t launch_step_lines(int q, int prec, const void* src, void* dst, const StepArgs& a,
+                             const double* e_src, double* e_dst, double* ue, const ElecArgs& ea,
+                             hipStream_t st);
+// (src, dst, StepArgs, e_src, e_dst, ue, ElecArgs)
+const void* lines_kernel_ptr(int q, int prec, int th_mode);
 // open x ends: the moments of the first and last node of every column of
 // src ([side][column][4] doubles), before the step that reads src
 hipError_t launch_open_moments(int q, int prec, const void* src, const StepArgs& a, double* bmom,
