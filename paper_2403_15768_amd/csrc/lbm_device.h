@@ -1103,4 +1103,27 @@ __device__ __forceinline__ void collide_store(const M* df, const StepArgs& a, LB
   });
 }
 
+// ------------------------------------------------------------------ lanes in different columns
+// the mixing weight of a wall node (0 elsewhere)
+template <typename M>
+__device__ __forceinline__ M wall_r(const StepArgs& a, uint32_t mask, int wallcol, int x) {
+  return (mask & kLinkBits) != 0u
+             ? gbl(static_cast<const M*>(a.rwall))[(int64_t)wallcol * a.nx + x]
+             : M(0);
+}
+
+// the wall rule of gather() for one link (its arithmetic, term by term)
+template <class L, typename S, typename M, bool BOUZ>
+__device__ __forceinline__ M wall_value(int i, const StepArgs& a, M gs, M gb, M r, M cb, M cc,
+                                        M behind, M own, int y) {
+  if (a.utop != 0.0 && L::cy[i] == -1 && y == a.ny - 1)
+    return gb + static_cast<M>(6.0 * L::w[i] * a.rho0 * L::cx[i] * a.utop);
+  M bb = gb;
+  if (BOUZ) {
+    if (cb != M(0)) bb += cb * (behind - gb);
+    if (cc != M(0)) bb += cc * (own - gb);
+  }
+  return gs + r * (bb - gs);
+}
+
 }  // namespace lbm

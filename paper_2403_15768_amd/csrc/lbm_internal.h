@@ -54,6 +54,7 @@ struct Plan {
   size_t off_bmom = 0;  // open ends: [side][column][4] moments of the end nodes
   size_t off_cols = 0, off_tiles = 0;
   lbm::BoxArgs box{};    // two steps per launch of a small D3Q19 channel (no blocks: none)
+  lbm::PairArgs pair{};  // two steps per launch of a large one in double (no tiles: none)
   std::vector<lbm::BoxTile> tiles;
   lbm::RunArgs run{};  // k steps per launch of a D2Q9 slab (k = 0: none)
   int64_t nsheet = 0;               // electron shell nodes (nshell nx)

@@ -1140,4 +1140,5 @@ hipError_t launch_set_r(int prec, const double* lambda, int64_t n, void* r, int*
 }  // namespace lbm
 
 #include "lbm_multistep.h"
+#include "lbm_pair.h"
 #include "lbm_quadrature.h"

@@ -43,6 +43,20 @@ struct BoxArgs {
 hipError_t launch_step_box(int prec, const void* src, void* dst, const StepArgs& a,
                            const BoxArgs& ba, bool bouz, hipStream_t st);
 const void* box_kernel_ptr(int prec, bool bouz, int cells);  // (src, dst, StepArgs, BoxArgs)
+// two steps per launch of a large D3Q19 channel in double (planar walls, no
+// noise, sheets, mask or open ends, populations of less than 4 GiB): tiles of
+// tx cells along x (whole x-lines where hx = 0, else with a halo lane on either
+// side) times one of `tiles` (its rows and a row on either side fit the lanes)
+struct PairArgs {
+  int ntiles, xtiles;  // all tiles; tiles along x (they vary fastest)
+  int tx, hx;
+  const BoxTile* tiles;
+  const ColInfo* cols;  // per box column
+};
+hipError_t launch_step_pair(const void* src, void* dst, const StepArgs& a, const PairArgs& pa,
+                            hipStream_t st);
+const void* pair_kernel_ptr();  // (src, dst, StepArgs, PairArgs)
+int pair_lanes();
 // k steps per launch of a D2Q9 slab without noise, sheets or open ends: tiles of tx x ty cells, in LDS
 // with k cells on every side (rx = tx + 2 k), or of whole x-lines (rx = tx =
 // nx); cells (1 or 2) per lane

@@ -96,3 +96,16 @@ def options(lbm, geo, nx, ny, nz):
 def test_boxes_equal_single_steps(lbm, geo, nx, ny, nz, precision):
     print("box", geo, nx, ny, nz, precision, flush=True)
     compare(lbm, geo, nx, ny, nz, precision, 1e-3 if geo == "slab" and nx == 64 else 0.0)
+
+
+# large channels in double: tiles of whole x-lines and of 32 cells, ragged last
+# tiles along x (padding), y and z, periodic z with a moving wall, one plane per
+# tile and more
+@pytest.mark.parametrize("geo,nx,ny,nz", [
+    ("duct", 32, 128, 64), ("duct", 40, 120, 60), ("duct", 127, 47, 45), ("duct", 128, 64, 33),
+    ("duct", 129, 64, 40), ("duct", 160, 41, 41), ("duct", 200, 37, 40), ("duct", 257, 26, 64),
+    ("slab", 320, 40, 21), ("slab", 1025, 130, 2), ("slab", 64, 16, 256),
+])
+def test_large_pairs_equal_single_steps(lbm, geo, nx, ny, nz):
+    print("pair", geo, nx, ny, nz, flush=True)
+    compare(lbm, geo, nx, ny, nz, "f64", 1e-3 if geo == "slab" else 0.0)
