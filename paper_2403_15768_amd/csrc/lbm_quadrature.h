@@ -258,21 +258,22 @@ __global__ void __launch_bounds__(kQuadThreads) k_friction_full(SpecArgs s,
 // Work: 129,024 nodes x 256 q x 20 multiply-adds and a table of up to 256 x
 // 256 panels x 20 points x 1024 omegas, instead of 129,024 x 262,144 points.
 // Measured (whole lbm_set_friction_spectral and lbm_get_friction): the R = 32
-// tube's 129,024 nodes 10.6 -> 0.56 ms, screened 32,256 nodes 5.6 -> 0.31 ms;
+// tube's 129,024 nodes 10.9 -> 0.43 ms, screened 32,256 nodes 5.8 -> 0.30 ms;
 // relative error against 64 bits unchanged (3e-16 to 4e-16).
 //
 // A table that would need more than kTabCap panels (poles close to the real
 // axis, or a very wide range of Omega) is not built: its q is summed term by
 // term inside k_quad_eval.
 constexpr int kTabDeg = 20;
-constexpr int kTabCap = 256;          // panels per table
+constexpr int kTabCap = 256;          // panels per table (one per lane of a block at most)
 constexpr int kTabGroup = 8;          // q points whose terms are summed first (fixed:
                                       // results do not depend on the scratch)
 constexpr double kPoleRatio = 4.2;
 constexpr int kRangeBlocks = 64;
 constexpr int kBuildPanels = 6;       // panels per block of k_quad_build
 constexpr int kBuildTile = 512;       // omega points per LDS tile
-constexpr int64_t kTabDoubles = (int64_t)kTabCap * kTabDeg;
+constexpr int64_t kTabDoubles = (int64_t)kTabCap * kTabDeg;  // [coefficient][panel]
+static_assert(kTabCap <= kQuadThreads, "a block loads one panel per lane");
 
 struct TabInfo {
   double s_lo, inv_h, h;
@@ -473,18 +474,18 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_build(SpecArgs s, int sha
     double m = 0.0;
     for (int i = kTabDeg - 1 - ((kTabDeg - 1 - k) & 1); i >= k; i -= 2)  // small terms first
       m += part[1][p * kTabDeg + i] * kCheb.c[i][k];
-    tab[(int64_t)blockIdx.y * kTabDoubles + (p0 + p) * kTabDeg + k] = m;
+    tab[(int64_t)blockIdx.y * kTabDoubles + k * kTabCap + p0 + p] = m;
   }
 }
 
 // One wall node per lane: the sums of q^3 e^{-2qd} P F_q over groups of
-// kTabGroup q points.  The q's table sits in LDS (neighbouring nodes have
-// nearly the same Omega, so a wave reads few different coefficients at a
-// time).  With rows, block row y takes one group and leaves its sum in
-// part[y]; without, one block adds `groups` of them to raw in order, as
-// k_quad_sum adds rows.
+// kTabGroup q points.  The q's table sits in LDS, coefficient by coefficient
+// (neighbouring nodes have nearly the same Omega, so the panels of a wave are
+// few and next to each other: the same place or different banks).  With part, block row y takes `per` groups and leaves the sum of
+// each in its row of part; without, one block adds all `groups` of them to
+// raw in order, as k_quad_sum adds rows.
 __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shared, int g0,
-                                                            int groups,
+                                                            int groups, int per,
                                                             const double* __restrict__ omega,
                                                             int64_t n,
                                                             const TabInfo* __restrict__ info,
@@ -500,8 +501,9 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shar
   const int64_t k = (int64_t)blockIdx.x * kQuadThreads + tid;
   const double om = fabs(k < n ? omega[k] : s.omega0);  // k >= n: reference or padding
   double sum = !part && g0 > 0 && k <= n ? raw[k] : 0.0;
-  for (int gi = 0; gi < (part ? 1 : groups); gi++) {
-    const int gl = part ? (int)blockIdx.y : gi;  // the group within this launch's tables
+  for (int gi = 0; gi < per; gi++) {
+    const int gl = (int)blockIdx.y * per + gi;  // the group within this launch's tables
+    if (gl >= groups) break;
     const int ga = (g0 + gl) * kTabGroup;        // its first q point
     const int na = min(kTabGroup, s.nq - ga);
     __syncthreads();
@@ -518,9 +520,11 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shar
       const TabInfo t = info[tb];
       if (!shared || (i == 0 && gi == 0)) {
         __syncthreads();
-        if (t.np <= kTabCap)
-          for (int e = tid; e < t.np * kTabDeg; e += kQuadThreads)
-            lds.c[e] = tab[(int64_t)tb * kTabDoubles + e];
+        if (t.np <= kTabCap && tid < t.np) {
+          const double* c = tab + (int64_t)tb * kTabDoubles + tid;
+#pragma unroll
+          for (int m = 0; m < kTabDeg; m++) lds.c[m * kTabCap + tid] = c[m * kTabCap];
+        }
         __syncthreads();
       }
       // P = Omega^2 (q d): rounded twice only (next to a resonance P - w^2
@@ -533,10 +537,10 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shar
         if (u >= 0.0 && u < (double)t.np + 0.5) {
           const int p = min((int)u, t.np - 1);
           const double x = 2.0 * (u - (double)p) - 1.0;
-          const double* c = lds.c + p * kTabDeg;
-          F = c[kTabDeg - 1];
+          const double* c = lds.c + p;
+          F = c[(kTabDeg - 1) * kTabCap];
 #pragma unroll
-          for (int m = kTabDeg - 2; m >= 0; m--) F = __builtin_fma(F, x, c[m]);
+          for (int m = kTabDeg - 2; m >= 0; m--) F = __builtin_fma(F, x, c[m * kTabCap]);
         }
       } else {
         F = 0.0;
@@ -551,11 +555,9 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shar
       acc += wt[i] * P * F;
     }
     sum += acc;
+    if (part && k <= n) part[(int64_t)gl * (n + 1) + k] = acc;
   }
-  if (k > n) return;
-  if (part)
-    part[(int64_t)blockIdx.y * (n + 1) + k] = sum;
-  else
+  if (!part && k <= n)
     raw[k] = g0 + groups >= (s.nq + kTabGroup - 1) / kTabGroup ? quad_scale(s) * sum : sum;
 }
 
@@ -626,8 +628,13 @@ hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, do
         hipLaunchKernelGGL(k_quad_build, dim3(kBuildX, (unsigned)tables), dim3(kQuadThreads), 0,
                            st, s, shared ? 1 : 0, g0 * kTabGroup, info, tab);
       }
-      hipLaunchKernelGGL(k_quad_eval, dim3(nblk, rows ? (unsigned)g : 1u), dim3(kQuadThreads), 0,
-                         st, s, shared ? 1 : 0, g0, g, omega, n, info, tab, part, raw);
+      // a shared table is loaded once per block: several groups each, as long
+      // as eight blocks per CU remain (129,024 nodes: 152 -> 133 us)
+      const int per =
+          !rows ? g : (shared ? (int)std::clamp<int64_t>((int64_t)nblk * g / 2048, 1, g) : 1);
+      hipLaunchKernelGGL(k_quad_eval, dim3(nblk, (unsigned)((g + per - 1) / per)),
+                         dim3(kQuadThreads), 0, st, s, shared ? 1 : 0, g0, g, per,
+                         omega, n, info, tab, part, raw);
       if (rows)
         hipLaunchKernelGGL(k_quad_sum, dim3(nblk), dim3(kQuadThreads), 0, st, s, g0 == 0 ? 1 : 0,
                            g0 + g == total ? 1 : 0, g, part, n, raw);
