@@ -36,8 +36,9 @@ HBM_PEAK_GBS = 8000.0
 BYTES_PER_UPDATE = {"f32": 152, "f64": 304, "f16s": 76}  # 19 reads + 19 writes
 DUCT = (256, 128, 64)
 KERNEL_SOURCES = ["paper_2403_15768_amd/csrc/lbm_device.h",
-                  "paper_2403_15768_amd/csrc/lbm_kernels.hip"]
-# counter-measured HBM bytes per launch of the dominant kernel, per workload
+                  "paper_2403_15768_amd/csrc/lbm_kernels.hip",
+                  "paper_2403_15768_amd/csrc/lbm_pair.h"]
+# counter-measured HBM bytes per step of the dominant kernel, per workload
 # and storage (no noise, periodic ends); used while the kernel sources match
 COUNTERS = {
     ("duct", "f32"): os.path.join(ROOT, "profiles",
@@ -218,7 +219,7 @@ def extras(torch, lbm, inputs, args):
     tb.set_friction_spectral(sp, om)
     qs = time.perf_counter() - t0
     n = tb.wall_count
-    out["quadrature"] = {"nodes": n, "grid": [sp.nq, sp.nw], "s": round(qs, 4),
+    out["quadrature"] = {"nodes": n, "grid": [sp.nq, sp.nw], "s": round(qs, 6),
                          "gpoints_per_s": round((n + 1) * sp.nq * sp.nw / qs / 1e9, 2)}
     # the screened form (|1 - g_s g_l e^{-2qd}|^2, dispersive liquid mode)
     sp.coupling, sp.v_l = 1, 0.5
@@ -227,7 +228,7 @@ def extras(torch, lbm, inputs, args):
     t0 = time.perf_counter()
     tb.set_friction_spectral(sp, om)
     qs = time.perf_counter() - t0
-    out["quadrature_screened"] = {"nodes": n, "grid": [sp.nq, sp.nw], "s": round(qs, 4),
+    out["quadrature_screened"] = {"nodes": n, "grid": [sp.nq, sp.nw], "s": round(qs, 6),
                                   "gpoints_per_s": round((n + 1) * sp.nq * sp.nw / qs / 1e9, 2)}
     sp.coupling, sp.v_l = 0, 0.0
     tb.set_friction_spectral(sp, om)
@@ -773,10 +774,12 @@ def main():
                      "traffic": traffic,
                      "traffic_GBs": None if traffic is None else round(traffic / kern_s / 1e9, 1),
                      "kernel": ("k_step_masked<D3Q19>" if corr else
+                                "k_step_pair (two steps per launch; bytes of two single steps)"
+                                if args.precision == "f64" and not args.thermal
+                                and not args.open_ends and not (slab and args.electrons) else
                                 "k_step<D3Q19>" if not args.thermal else
                                 f"k_step<D3Q19, noise {args.thermal}>")
-                               + (" + k_electron_step (time per step covers both)"
-                                  if slab and args.electrons else "")
+                               + (", k_step_lines with the sheets" if slab and args.electrons else "")
                                + (" + k_open_ends (time per step covers both)"
                                   if args.open_ends else ""),
                      "kernel_us": round(kern_s * 1e6, 3), "bytes_per_update": bpu},

@@ -179,7 +179,9 @@ lbm_status lbm_set_friction(lbm_ctx *ctx, const double *lambda, size_t n,
  * (appendix, Eq. 27) as a (q, omega) sum over the two surfaces' response
  * spectra (lbm_spectral above), the plasmon frequency standing for the
  * charge-carrier density of Sec. 5.1.  Host or device Omega (finite, >= 0,
- * else LBM_EINVAL); bad spectral parameters -> LBM_EINVAL.  Synchronous. */
+ * else LBM_EINVAL); bad spectral parameters -> LBM_EINVAL.  Synchronous.
+ * The buffer that the next step overwrites serves as scratch (as for
+ * lbm_get_field). */
 lbm_status lbm_set_friction_spectral(lbm_ctx *ctx, const lbm_spectral *sp,
                                      const double *omega, size_t n,
                                      int on_device);

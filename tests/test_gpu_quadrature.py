@@ -121,3 +121,32 @@ def test_a_bad_frequency_stays_its_own(lbm, coupling):
     rest[[7, 4000]] = False
     # (the two nodes' own frequencies may have set the ends of the range)
     assert np.max(np.abs(got[rest] / clean[rest] - 1)) < 2 * TOL
+
+
+@pytest.mark.parametrize("coupling,n", [(0, 5000), (1, 20000)])
+def test_static_call_in_a_graph(lbm, coupling, n):
+    # captured once, replayed between eager calls on other frequencies: every
+    # replay gives the eager call's bits
+    import torch
+
+    print("static quadrature in a graph", coupling, n, flush=True)
+    sp = spectra(32, 64, coupling, 0.0, 1)
+    s = lbm.make_spectral(sp)
+    om = [sp.omega0 * np.random.default_rng(k).uniform(0.5, 1.5, n) for k in (6, 7, 8)]
+    eager = [static(lbm, sp, o) for o in om]
+    d_om = torch.zeros(n, dtype=torch.float64, device="cuda")
+    d_lam = torch.zeros(n, dtype=torch.float64, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rc = lbm.load().lbm_friction_quadrature_static(
+            C.byref(s), C.c_void_p(d_om.data_ptr()), n, C.c_void_p(d_lam.data_ptr()),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    for o, want in zip(om, eager):
+        d_om.copy_(torch.tensor(o, dtype=torch.float64))
+        d_lam.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(d_lam.cpu().numpy(), want)
+        static(lbm, sp, om[0][::-1].copy())
