@@ -558,8 +558,8 @@ lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
   pl.off_shellof = take(pl.shellof.size() * sizeof(int32_t));
   pl.off_cellw = take(pl.cellw.size() * sizeof(int32_t));
   pl.off_rowx = take(pl.rowx.size() * sizeof(int32_t));
-  // open ends: per population buffer, [side][column][4] records of the end nodes
-  pl.off_bmom = take((size_t)2 * 2 * pl.ncolbox * 4 * sizeof(double));
+  // open ends: per population buffer, the records of the end nodes
+  pl.off_bmom = take((size_t)2 * 2 * pl.ncolbox * lbm::kEndSlots * sizeof(double));
   pl.off_ptab = take(pl.ptab.size());
   pl.off_cols = take(pl.run.k || !pl.tiles.empty() ? pl.colinfo.size() * sizeof(ColInfo) : 0);
   pl.off_tiles = take(pl.tiles.size() * sizeof(lbm::BoxTile));

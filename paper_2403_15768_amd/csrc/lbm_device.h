@@ -132,10 +132,10 @@ struct StepArgs {
   const uint8_t* ptab;
   int64_t nw2d;
   // open x ends (0: periodic): prescribed density deviations rho - rho0 of
-  // the ghost planes x = -1 (inlet) and x = nx (outlet); records
-  // (sum g, u_x, u_y, u_z) of the stored populations of the first and the
-  // last node of every column, [side][column][4], of the buffer the step
-  // reads (bmom) and of the one it writes (bmom_out)
+  // the ghost planes x = -1 (inlet) and x = nx (outlet); records of the
+  // ghosts beside the first and the last node of every column,
+  // [side][column][kEndSlots] (see end_shifts), of the buffer the step reads
+  // (bmom) and of the one it writes (bmom_out)
   int open;
   double drho_in, drho_out;
   const double* bmom;
@@ -735,11 +735,43 @@ __device__ __forceinline__ void open_patch(const S* __restrict__ g0, const StepA
   }
 }
 
-// Record of one end node for the open-end ghosts: drho = sum_k g_k and
-// u = sum_k g_k c_k / (rho0 + drho) of its stored populations (gc: the
-// column's base, x its cell), written to o[0..3].  Summed in the order the
-// step kernel's collide_store<REC> sums what it stores (rest, then each
-// opposite pair), so that a state set from outside continues bit for bit.
+// What the ghost beside an end node adds to the node's own population of a
+// direction k into the channel (c_kx > 0 at the first node, c_kx < 0 at the
+// last),
+//   w_k (drho_bc - drho_b) (1 + 3 c_k.u_b + 4.5 (c_k.u_b)^2 - 1.5 u_b.u_b),
+// from drho_b = sum_m g_m(b) and u_b = sum_m g_m(b) c_m / (rho0 + drho_b) of
+// the populations stored there: the record o of that node, one value per
+// direction of its side.  The step that stores the populations forms it, after
+// its stores: when the next step formed it, four values for each of five
+// source columns had to arrive first.
+constexpr int kEndSlots = 5;
+template <class L>
+constexpr int end_slot(int k) {  // among the directions of its c_x
+  int n = 0;
+  for (int j = 0; j < k; j++)
+    if (L::cx[j] == L::cx[k]) n++;
+  return n;
+}
+template <class L, typename M>
+__device__ __forceinline__ void end_shifts(const StepArgs& a, bool at_in, M drho, M jx, M jy, M jz,
+                                           LBM_GLOBAL double* o) {
+  const M rho = static_cast<M>(a.rho0) + drho;
+  const M ux = jx / rho, uy = jy / rho, uz = jz / rho;
+  const M usq = ux * ux + uy * uy + uz * uz;
+  const M dbc = static_cast<M>(at_in ? a.drho_in : a.drho_out);
+#pragma unroll
+  for (int k = 0; k < L::Q; k++) {
+    if (L::cx[k] == 0 || (L::cx[k] > 0) != at_in) continue;
+    const M cu = cdot<L, M>(k, ux, uy, uz);
+    o[end_slot<L>(k)] = static_cast<double>(
+        static_cast<M>(L::w[k]) * (dbc - drho) *
+        (M(1) + M(3) * cu + M(4.5) * cu * cu - M(1.5) * usq));
+  }
+}
+
+// Record of one end node (gc: the column's base, x its cell).  Summed in the
+// order the step kernel's collide_store<REC> sums what it stores (rest, then
+// each opposite pair), so that a state set from outside continues bit for bit.
 template <class L, typename S, typename M>
 __device__ __forceinline__ void end_record(const LBM_GLOBAL S* gc, const StepArgs& a, unsigned x,
                                            LBM_GLOBAL double* o) {
@@ -755,49 +787,58 @@ __device__ __forceinline__ void end_record(const LBM_GLOBAL S* gc, const StepArg
     if (L::cy[i]) jy += L::cy[i] > 0 ? dd : -dd;
     if (L::cz[i]) jz += L::cz[i] > 0 ? dd : -dd;
   }
-  const M rho = static_cast<M>(a.rho0) + r0;
-  o[0] = static_cast<double>(r0);
-  o[1] = static_cast<double>(jx / rho);
-  o[2] = static_cast<double>(jy / rho);
-  o[3] = static_cast<double>(jz / rho);
+  end_shifts<L, M>(a, x == 0u, r0, jx, jy, jz, o);
 }
 
-// The rest of the ghost for the step kernel (whose OPEN gather already
-// read g_i(b)): for the first (last) node of an x-line, each fluid link that
-// would pull from x = -1 (x = nx) gains
-//   w_i (drho_bc - drho_b) (1 + 3 c_i.u_b + 4.5 (c_i.u_b)^2 - 1.5 u_b.u_b)
-// from b's record (bmom: the records of the buffer the step reads,
-// [side][column][4]).  Lanes inside the line return at once.
+// The rest of the ghosts for the step kernel (whose OPEN gather reads
+// g_i(b)): open_load takes the records' values for the links of the first
+// (last) node of an x-line that pull from x = -1 (x = nx) (bmom: the records
+// of the buffer the step reads); open_correct, after the gather, adds them to
+// the fluid ones among those links.  Half storage (sh null) reads them there
+// one by one: taken together they cost it 1 to 2.5 % on small channels, where
+// float and double gain 5 to 10 %.
+template <class L, typename M>
+__device__ __forceinline__ void open_load(const StepArgs& a, const double* bmom, int col, int x,
+                                          M* sh) {
+  const bool in = x == 0, out = x == a.nx - 1;
+  if (!in && !out) return;
+  const int z = col / a.ny;
+  const int y = col - z * a.ny;
+  const LBM_GLOBAL double* bm = gbl(bmom) + (in ? 0 : (int64_t)a.ny * a.nz * kEndSlots);
+#pragma unroll
+  for (int i = 0; i < L::Q; i++) {
+    if (L::cx[i] == 0 || (L::cx[i] > 0) != in) continue;
+    const int ys = y - L::cy[i];
+    if (ys < 0 || ys >= a.ny) continue;  // a wall link
+    int zb = z - L::cz[i];
+    if (zb < 0) zb += a.nz;  // z periodic (a duct or tube: a wall link)
+    if (zb >= a.nz) zb -= a.nz;
+    sh[end_slot<L>(i)] =
+        static_cast<M>(bm[((int64_t)ys + (int64_t)a.ny * zb) * kEndSlots + end_slot<L>(i)]);
+  }
+}
 template <class L, typename M, bool BOUZ = false>
 __device__ __forceinline__ void open_correct(const StepArgs& a, const double* bmom, int col, int x,
-                                             ColInfo info, M* df) {
+                                             ColInfo info, const M* sh, M* df) {
   const bool in = x == 0, out = x == a.nx - 1;
   if (!in && !out) return;
   const uint32_t mask = info.mask;
   const int z = col / a.ny;
   const int y = col - z * a.ny;
-  const LBM_GLOBAL double* bm_in = gbl(bmom);
-  const LBM_GLOBAL double* bm_out = bm_in + (int64_t)a.ny * a.nz * 4;
-  // w_k (drho_bc - drho_b) (1 + 3 c_k.u_b + 4.5 (c_k.u_b)^2 - 1.5 u_b.u_b)
-  auto shift = [&](const LBM_GLOBAL double* r, int k, bool at_in) {
-    const M drho = static_cast<M>(r[0]);
-    const M ux_ = static_cast<M>(r[1]), uy_ = static_cast<M>(r[2]), uz_ = static_cast<M>(r[3]);
-    const M cu = cdot<L, M>(k, ux_, uy_, uz_);
-    const M usq = ux_ * ux_ + uy_ * uy_ + uz_ * uz_;
-    const M dbc = static_cast<M>(at_in ? a.drho_in : a.drho_out);
-    return static_cast<M>(L::w[k]) * (dbc - drho) *
-           (M(1) + M(3) * cu + M(4.5) * cu * cu - M(1.5) * usq);
-  };
+  const LBM_GLOBAL double* bm = gbl(bmom) + (in ? 0 : (int64_t)a.ny * a.nz * kEndSlots);
 #pragma unroll
   for (int i = 0; i < L::Q; i++) {
     if (L::cx[i] == 0 || (mask & (1u << i))) continue;
-    if (!((L::cx[i] > 0 && in) || (L::cx[i] < 0 && out))) continue;
+    if ((L::cx[i] > 0) != in) continue;
+    if (sh) {
+      df[i] += sh[end_slot<L>(i)];
+      continue;
+    }
     int zb = z - L::cz[i];
-    if (zb < 0) zb += a.nz;  // z periodic (slab; a duct or tube never pulls across z)
+    if (zb < 0) zb += a.nz;
     if (zb >= a.nz) zb -= a.nz;
-    const LBM_GLOBAL double* r = (in ? bm_in : bm_out) +
-                                 ((int64_t)(y - L::cy[i]) + (int64_t)a.ny * zb) * 4;
-    df[i] += shift(r, i, in);
+    df[i] += static_cast<M>(
+        bm[((int64_t)(y - L::cy[i]) + (int64_t)a.ny * zb) * kEndSlots + end_slot<L>(i)]);
   }
   if constexpr (BOUZ) {
     // interpolated wall links whose node behind, x + c_i, lies beyond this
@@ -809,11 +850,11 @@ __device__ __forceinline__ void open_correct(const StepArgs& a, const double* bm
 #pragma unroll
     for (int i = 0; i < L::Q; i++) {
       if (L::cx[i] == 0 || !(mask & (1u << i))) continue;
-      if (!((L::cx[i] > 0 && out) || (L::cx[i] < 0 && in))) continue;
+      if ((L::cx[i] < 0) != in) continue;
       const M cbz = cw[2 * i];
       if (cbz == M(0)) continue;
       const int64_t nc = (int64_t)(y + L::cy[i]) + (int64_t)a.ny * (z + L::cz[i]);
-      df[i] += rw * cbz * shift((in ? bm_in : bm_out) + nc * 4, L::opp[i], in);
+      df[i] += rw * cbz * static_cast<M>(bm[nc * kEndSlots + end_slot<L>(L::opp[i])]);
     }
   }
 }

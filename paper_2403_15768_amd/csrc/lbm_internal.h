@@ -51,7 +51,7 @@ struct Plan {
   int64_t nwallslots = 0;  // leading slots whose columns hold wall nodes
   std::vector<int32_t> rowx;  // per wall row: count, then the x of its points ([y][nxp + 1])
   size_t off_cellw = 0, off_ptab = 0, off_rowx = 0;
-  size_t off_bmom = 0;  // open ends: [side][column][4] moments of the end nodes
+  size_t off_bmom = 0;  // open ends: [side][column][kEndSlots] records of the end nodes
   size_t off_cols = 0, off_tiles = 0;
   lbm::BoxArgs box{};    // two steps per launch of a small D3Q19 channel (no blocks: none)
   lbm::PairArgs pair{};  // two steps per launch of a large one in double (no tiles: none)
@@ -142,9 +142,9 @@ inline lbm::SpecArgs spec_args(const lbm_spectral* sp) {
                        sp->w_max, sp->lambda_target, sp->dispersion, sp->coupling, sp->v_l};
 }
 lbm_status sync(lbm_ctx* c);
-// open ends: the end-node records ([side][column][4]) of population buffer b
+// open ends: the end-node records ([side][column][kEndSlots]) of population buffer b
 inline double* end_records(lbm_ctx* c, int b) {
-  return c->at<double>(c->pl.off_bmom) + (size_t)b * 2 * c->pl.ncolbox * 4;
+  return c->at<double>(c->pl.off_bmom) + (size_t)b * 2 * c->pl.ncolbox * lbm::kEndSlots;
 }
 // rebuild the records of the current buffer if no step has left them
 // (asynchronous, on the context's stream)

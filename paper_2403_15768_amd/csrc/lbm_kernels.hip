@@ -53,8 +53,18 @@ __device__ __forceinline__ void step_cell(const S* __restrict__ src, S* __restri
   M xi[L::Q];
   if constexpr (TH != 0)
     thermal_noise<L, M, TH, NormalT<S>>(a, (uint32_t)col * (uint32_t)a.nx + (uint32_t)x, step, xi);
+  // open ends: the ghosts' values, in flight with the gather in float storage
+  // (256 x 128 x 64 duct 63.4 -> 58.6 us, smaller ones by 5 to 10 %); in double
+  // and on tubes the registers they hold cost more (115.9 -> 117.4, tube 45.3
+  // -> 46.8)
+  constexpr bool kEarly = OPEN && !BOUZ && sizeof(S) == 4;
+  M sh[kEndSlots];
+  if constexpr (kEarly) open_load<L, M>(a, a.bmom, col, xc, sh);
   gather<L, S, M, M, BOUZ, ELEC, OPEN>(src, a, col, xc, info, df);
-  if constexpr (OPEN) open_correct<L, M, BOUZ>(a, a.bmom, col, xc, info, df);
+  if constexpr (OPEN) {
+    if constexpr (!kEarly && sizeof(S) != 2) open_load<L, M>(a, a.bmom, col, xc, sh);
+    open_correct<L, M, BOUZ>(a, a.bmom, col, xc, info, sizeof(S) != 2 ? sh : nullptr, df);
+  }
   if constexpr (CHECK) {
     if (x < a.nx) {
       double dr = 0, jx = 0;
@@ -74,15 +84,10 @@ __device__ __forceinline__ void step_cell(const S* __restrict__ src, S* __restri
   // open ends: the end nodes leave the record of what they stored (the same
   // sums end_record forms) for the ghosts of the next step
   if constexpr (OPEN)
-    if (x == xc && (x == 0 || x == a.nx - 1)) {
-      LBM_GLOBAL double* o =
-          gbl(a.bmom_out) + ((x == 0 ? 0 : (int64_t)a.ny * a.nz) + col) * 4;
-      const M rho = static_cast<M>(a.rho0) + rec[0];
-      o[0] = static_cast<double>(rec[0]);
-      o[1] = static_cast<double>(rec[1] / rho);
-      o[2] = static_cast<double>(rec[2] / rho);
-      o[3] = static_cast<double>(rec[3] / rho);
-    }
+    if (x == xc && (x == 0 || x == a.nx - 1))
+      end_shifts<L, M>(a, x == 0, rec[0], rec[1], rec[2], rec[3],
+                       gbl(a.bmom_out) +
+                           ((x == 0 ? 0 : (int64_t)a.ny * a.nz) + col) * kEndSlots);
 }
 
 // Per-block partial sums (s0, s1) over a block of the step or moments grid:
@@ -201,26 +206,23 @@ __global__ void __launch_bounds__(512) k_step_masked(const S* __restrict__ src,
     ColInfo info;
     info.wallcol = 0;
     info.mask = wl;
-    open_correct<L, M>(a, a.bmom, col, xc, info, df);
+    M sh[kEndSlots];
+    if constexpr (sizeof(S) != 2) open_load<L, M>(a, a.bmom, col, xc, sh);
+    open_correct<L, M>(a, a.bmom, col, xc, info, sizeof(S) != 2 ? sh : nullptr, df);
   }
   M rec[4];
   collide_store<L, M, S, TH, OPEN>(df, a, gbl(dst) + (int64_t)col * a.sC, (unsigned)x,
                                    (uint32_t)col * (uint32_t)a.nx + (uint32_t)x, step, xi, rec);
   if constexpr (OPEN)
-    if (x == xc && (x == 0 || x == a.nx - 1)) {
-      LBM_GLOBAL double* o =
-          gbl(a.bmom_out) + ((x == 0 ? 0 : (int64_t)a.ny * a.nz) + col) * 4;
-      const M rho = static_cast<M>(a.rho0) + rec[0];
-      o[0] = static_cast<double>(rec[0]);
-      o[1] = static_cast<double>(rec[1] / rho);
-      o[2] = static_cast<double>(rec[2] / rho);
-      o[3] = static_cast<double>(rec[3] / rho);
-    }
+    if (x == xc && (x == 0 || x == a.nx - 1))
+      end_shifts<L, M>(a, x == 0, rec[0], rec[1], rec[2], rec[3],
+                       gbl(a.bmom_out) +
+                           ((x == 0 ? 0 : (int64_t)a.ny * a.nz) + col) * kEndSlots);
 }
 
-// Open x ends: the records (sum g, u) of the first and last node of every
-// fluid column of src ([side][column][4]) where no step has left them (after
-// the state was set from outside).  One lane per (column, side).
+// Open x ends: the records of the first and last node of every fluid column
+// of src ([side][column][kEndSlots]) where no step has left them (after the
+// state was set from outside).  One lane per (column, side).
 template <class L, typename S, typename M>
 __global__ void __launch_bounds__(256) k_open_moments(const S* __restrict__ src, StepArgs a,
                                                       double* __restrict__ bmom) {
@@ -230,7 +232,7 @@ __global__ void __launch_bounds__(256) k_open_moments(const S* __restrict__ src,
   const int col = gbl(a.slots)[t >> 1].col;
   const unsigned x = side ? (unsigned)a.nx - 1u : 0u;
   end_record<L, S, M>(gbl(src) + (int64_t)col * a.sC, a, x,
-                      gbl(bmom) + ((int64_t)side * a.ny * a.nz + col) * 4);
+                      gbl(bmom) + ((int64_t)side * a.ny * a.nz + col) * kEndSlots);
 }
 
 // ------------------------------------------------------------ electron sheets
@@ -660,24 +662,24 @@ __global__ void __launch_bounds__(512) k_batch_step(const MemberDesc* __restrict
   if constexpr (TH != 0)
     thermal_noise<L, M, TH, NormalT<S>>(a, (uint32_t)c.col * (uint32_t)a.nx + (uint32_t)c.x, d.base_step + k,
                             xi);
-  gather<L, S, M, M, BOUZ, ELEC, OPEN>(src, a, colA, xc, info, df, c.dl);
   // open ends: the ghosts from the records of the buffer read (the lane's own
   // column: runs of plain columns have no wall links or z wrap)
-  if constexpr (OPEN) open_correct<L, M, BOUZ>(a, d.bmom[odd ? 1 : 0], c.col, xc, info, df);
+  gather<L, S, M, M, BOUZ, ELEC, OPEN>(src, a, colA, xc, info, df, c.dl);
+  if constexpr (OPEN) {
+    M sh[kEndSlots];
+    if constexpr (sizeof(S) != 2) open_load<L, M>(a, d.bmom[odd ? 1 : 0], c.col, xc, sh);
+    open_correct<L, M, BOUZ>(a, d.bmom[odd ? 1 : 0], c.col, xc, info,
+                             sizeof(S) != 2 ? sh : nullptr, df);
+  }
   M rec[4];
   collide_store<L, M, S, TH, OPEN>(df, a, gbl(dst) + (int64_t)colA * a.sC, c.dl + (unsigned)c.x,
                                    (uint32_t)c.col * (uint32_t)a.nx + (uint32_t)c.x,
                                    d.base_step + k, xi, rec);
   if constexpr (OPEN)
-    if (c.x == xc && (c.x == 0 || c.x == a.nx - 1)) {
-      LBM_GLOBAL double* o = gbl(d.bmom[odd ? 0 : 1]) +
-                             ((c.x == 0 ? 0 : (int64_t)a.ny * a.nz) + c.col) * 4;
-      const M rho = static_cast<M>(a.rho0) + rec[0];
-      o[0] = static_cast<double>(rec[0]);
-      o[1] = static_cast<double>(rec[1] / rho);
-      o[2] = static_cast<double>(rec[2] / rho);
-      o[3] = static_cast<double>(rec[3] / rho);
-    }
+    if (c.x == xc && (c.x == 0 || c.x == a.nx - 1))
+      end_shifts<L, M>(a, c.x == 0, rec[0], rec[1], rec[2], rec[3],
+                       gbl(d.bmom[odd ? 0 : 1]) +
+                           ((c.x == 0 ? 0 : (int64_t)a.ny * a.nz) + c.col) * kEndSlots);
 }
 
 // per-item partial sums of (j_x, rho - rho0) of items [first, first + count);
