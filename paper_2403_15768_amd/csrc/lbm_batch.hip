@@ -65,6 +65,7 @@ struct lbm_batch {
   // holds for each
   std::vector<lbm_ctx*> m;
   std::vector<int64_t> base;  // step of the member when the device counter was 0
+  std::vector<int32_t> cur_base;  // its current buffer then, by the parity of the counter
   std::vector<double> th_amp;
   std::vector<uint64_t> th_seed;
   std::vector<std::array<double, 6>> th_fac;
@@ -463,6 +464,7 @@ lbm_status write_desc(lbm_batch* b, int s) {
                          b->stream));
   BCHK(b, hipStreamSynchronize(b->stream));
   b->base[s] = d.base_step;
+  b->cur_base[s] = d.cur_base;
   b->th_amp[s] = c->args.th_amp;
   b->th_seed[s] = c->args.th_seed;
   std::copy(c->args.th_fac, c->args.th_fac + 6, b->th_fac[s].begin());
@@ -481,12 +483,15 @@ bool same_lines(const lbm::ElecArgs& a, const lbm::ElecArgs& e) {
 }
 
 // A member stepped, restored or overwritten outside the batch no longer sits
-// at base + k: rewrite its table entry.
+// at base + k, or no longer in the buffer that the entry has there (a launch
+// of several steps swaps the buffers once, so a member restored to its old
+// step count may sit in either): rewrite its table entry.
 lbm_status resync(lbm_batch* b) {
   for (size_t s = 0; s < b->m.size(); s++) {
     const lbm_ctx* c = b->m[s];
     if (!c) continue;
-    if (c->step == b->base[s] + b->k && c->args.th_amp == b->th_amp[s] &&
+    if (c->step == b->base[s] + b->k && ((b->cur_base[s] + b->k) & 1) == c->cur &&
+        c->args.th_amp == b->th_amp[s] &&
         c->args.th_seed == b->th_seed[s] &&
         std::equal(b->th_fac[s].begin(), b->th_fac[s].end(), c->args.th_fac) &&
         c->args.drho_in == b->ends[s][0] && c->args.drho_out == b->ends[s][1] &&
@@ -715,6 +720,7 @@ lbm_status init_batch(lbm_batch* b, void* arena, size_t arena_bytes, void* hip_s
   b->stream = reinterpret_cast<hipStream_t>(hip_stream);
   b->m.assign(b->cap_members, nullptr);
   b->base.assign(b->cap_members, 0);
+  b->cur_base.assign(b->cap_members, 0);
   b->th_amp.assign(b->cap_members, 0.0);
   b->th_seed.assign(b->cap_members, 0);
   b->th_fac.assign(b->cap_members, std::array<double, 6>{});

@@ -252,6 +252,41 @@ def test_batch_members_stepped_outside(lbm):
     b.close()
 
 
+@pytest.mark.parametrize("outside", [1, 2, 70])
+@pytest.mark.parametrize("precision", ["f64", "f32", "f16s"])
+def test_batch_members_put_back_to_their_step(lbm, precision, outside):
+    """Members advanced on their own and put back to the step count at which
+    the batch left them: two steps may have been one launch and one swap of
+    the buffers, so the batch has to look where the state is."""
+    say("batch with members put back", precision, outside)
+    chans = make_ducts(lbm, SPECS, precision)
+    ref = make_ducts(lbm, SPECS, precision)
+    other = make_ducts(lbm, SPECS, precision)
+    b = lbm.Batch(chans)
+    b.step(10)
+    for r, o in zip(ref, other):
+        r.step(10)
+        o.step(13)
+    same = chans[0].get_state()
+    for c in chans[:4]:
+        c.step(outside)
+    chans[0].set_state(*same)  # the same state ...
+    for r in (chans[1], ref[1]):
+        r.set_state(other[1].get_state()[0], 10)  # ... another one
+    for r in (chans[2], ref[2]):
+        r.set_populations(other[2].populations(), 10)
+    ref[3].step(outside)  # left where it is
+    b.step(5)
+    inv_b = b.invariants()
+    for k, (c, r) in enumerate(zip(chans, ref)):
+        r.step(5)
+        assert c.step_count == r.step_count == (15 + outside if k == 3 else 15)
+        assert np.array_equal(c.get_state()[0], r.get_state()[0]), k
+        assert np.array_equal(c.field(1), r.field(1)), k
+        assert abs(inv_b[k, 0] / r.flux() - 1) < 1e-13
+    b.close()
+
+
 @pytest.mark.parametrize("precision", ["f32", "f16s"])
 def test_batch_groups_do_not_change_results(lbm, precision):
     """Members cut into several groups (each run 64 steps before the next)
