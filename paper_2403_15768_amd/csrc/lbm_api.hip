@@ -729,6 +729,13 @@ lbm_status lbm_host::launch_one_step(lbm_ctx* c, bool check) {
 
 namespace {
 
+// Whether the context's stream is being captured into a graph of the caller's.
+bool captured(const lbm_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (c->stream && hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
+}
+
 // How many plain steps one launch takes (1: the step kernel).
 int steps_per_launch(const lbm_ctx* c) {
   if (c->elec || c->args.open || c->args.th_mode != 0) return 1;
@@ -945,7 +952,12 @@ lbm_status do_steps(lbm_ctx* c, int64_t n) {
     c->dstep_value += kGraphSteps;
     n -= kGraphSteps;
   }
-  for (const int per = steps_per_launch(c); n >= 2 && per > 1;) {
+  // An even number of steps captured by the caller is replayed from the buffer
+  // that was current then: one swap of the buffers per step brings the state
+  // back there, in the capture and in every later call (a graph of ours swaps
+  // an even number of times); one swap per launch would not.
+  if (captured(c)) c->replayed = true;
+  for (const int per = c->replayed ? 1 : steps_per_launch(c); n >= 2 && per > 1;) {
     const int k = (int)std::min<int64_t>(n, per);
     lbm_status s = launch_steps(c, k);
     if (s != LBM_OK) return s;

@@ -87,6 +87,7 @@ struct lbm_ctx {
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   bool graphs_ok = true;
+  bool replayed = false;  // steps were captured into a graph of the caller's
   int64_t dstep_value = 0;  // value the device step base holds after enqueued work
   double kT = 0.0;          // lattice temperature of the thermal noise (0: none)
   bool elec = false;        // electron sheets on (SLAB)

@@ -109,3 +109,34 @@ def test_boxes_equal_single_steps(lbm, geo, nx, ny, nz, precision):
 def test_large_pairs_equal_single_steps(lbm, geo, nx, ny, nz):
     print("pair", geo, nx, ny, nz, flush=True)
     compare(lbm, geo, nx, ny, nz, "f64", 1e-3 if geo == "slab" else 0.0)
+
+
+# an even number of steps, captured and replayed with eager steps in between:
+# every replay starts from the buffer where the one before left the state
+@pytest.mark.parametrize("geo,nx,ny,nz,n", [
+    ("plane", 64, 30, 1, 2), ("plane", 64, 30, 1, 16), ("duct", 20, 17, 30, 2),
+    ("duct", 20, 17, 30, 6), ("tube", 16, 8, 0, 2), ("duct", 32, 128, 64, 2),
+])
+def test_captured_steps_replay(lbm, geo, nx, ny, nz, n):
+    import torch
+
+    print("captured steps", geo, nx, ny, nz, n, flush=True)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        A, B = (channel(lbm, geo, nx, ny, nz, "f64") for _ in range(2))
+    A.step(3)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        A.step(n)
+    total = 3
+    for eager in (0, 2, 66, 0):
+        A.step(eager)
+        s.synchronize()
+        with torch.cuda.stream(s):
+            graph.replay()
+        s.synchronize()
+        total += eager + n
+        B.step(total - B.step_count)
+        assert np.array_equal(A.populations(), B.populations()), (eager, total)
+    assert np.isfinite(A.flux()) and A.flux() == B.flux()
