@@ -247,11 +247,12 @@ __global__ void __launch_bounds__(kQuadThreads) k_friction_full(SpecArgs s,
 // conjugates.  The nodes need F_q on [Omega_min, Omega_max] sqrt(q d) only;
 // there it is cut into equal panels, each a polynomial of degree
 // kTabDeg - 1 through the Chebyshev points.  With every pole at least
-// kPoleRatio half-widths from every panel, the ellipse of parameter
-// rho = k + sqrt(k^2 + 1) = 8.5 around a panel holds no pole, and the
-// interpolation error, about rho^-20 = 2e-19 relative (each term is
-// positive, so the terms' relative errors do not add up), is far below a
-// double's rounding.  The same bound keeps the monomial form in the panel's
+// kPoleRatio half-widths from every panel's centre, the ellipse of parameter
+// rho = k + sqrt(k^2 - 1) = 8.3 or more around a panel holds no pole.  For a
+// pair of poles at the axis, 1 / (k - x)^2, the relative interpolation error
+// is at most 2 rho^-20 (1 + 20 (k + 1) / sqrt(k^2 - 1)) = 2e-17 (each term is
+// positive, so the terms' relative errors do not add up), below a double's
+// rounding.  The same bound keeps the monomial form in the panel's
 // own coordinate well conditioned (its coefficients fall like 4.2^-j).
 // Without screening and with v_l = 0, F does not depend on q: one table.
 //
@@ -390,12 +391,15 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_plan(SpecArgs s, int shar
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < kQuadThreads / 64; w++) d = fmin(d, red[w]);
+    // panels of at most that width, none beyond the range (there the poles may
+    // be closer); a range of one point: a panel around it
+    const double widest = 2.0 * d / kPoleRatio, range_s = s_hi - s_lo;
+    const double np = ceil(range_s / widest);
     TabInfo t;
-    t.s_lo = s_lo;
-    t.h = 2.0 * d / kPoleRatio;
+    t.np = np <= (double)kTabCap && widest < INFINITY ? max(1, (int)np) : kTabCap + 1;
+    t.h = range_s > 0.0 ? range_s / t.np : widest;
     t.inv_h = 1.0 / t.h;
-    const double np = (s_hi - s_lo) * t.inv_h;
-    t.np = np <= (double)kTabCap && t.h < INFINITY ? max(1, (int)ceil(np)) : kTabCap + 1;
+    t.s_lo = range_s > 0.0 ? s_lo : s_lo - 0.5 * t.h;
     t.pad = 0;
     info[blockIdx.x] = t;
   }

@@ -150,3 +150,41 @@ def test_static_call_in_a_graph(lbm, coupling, n):
         torch.cuda.synchronize()
         assert np.array_equal(d_lam.cpu().numpy(), want)
         static(lbm, sp, om[0][::-1].copy())
+
+
+# nearly equal frequencies (or one), all beyond the poles: the panels must not
+# reach past the frequencies towards a pole.  Against the node-by-node kernel
+# that fewer nodes take, whose factors outside the omega sum are the same; the
+# rest differs by the roundings of v (4 u), of the denominator and its
+# reciprocal (4 u), of the polynomial (4 u) and of the products (2 u),
+# u = 1.1e-16
+@pytest.mark.parametrize("lo,hi,w_max", [(1.0, 1.001, 3.0), (1.5, 1.5, 4.0), (1.0, 1.4, 4.0),
+                                         (2.5, 2.501, 3.0)])
+@pytest.mark.parametrize("coupling", [0, 1])
+def test_panels_stay_inside_the_frequencies(lbm, lo, hi, w_max, coupling):
+    print("panels", lo, hi, w_max, coupling, flush=True)
+    sp = spectra(16, 1, coupling, 0.0, 0, gamma_s=2.0 ** -10)
+    sp.T, sp.omega0, sp.omega_l, sp.gamma_l, sp.a_l, sp.d = 0.5, lo, 1.0, 0.5, 0.5, 1.0
+    raw = {}
+    few, many = ((42, 43), (307, 308))[coupling]
+    om = np.linspace(lo, hi, 60 * few)
+    for nx in (few, many):  # node by node; piecewise
+        G = lbm.Channel(19, lbm.DUCT, nx, 16, 16, tau=0.7, precision="f16s")
+        n = G.wall_count
+        G.set_friction_spectral(make_w(sp, w_max), np.resize(om, n))
+        raw[nx] = G.get_friction(raw=True)[1][: len(om)]
+    assert np.all(raw[few] > 0)
+    err = np.max(np.abs(raw[many] / raw[few] - 1))
+    print(f"  {err:.2e}", flush=True)
+    assert err < 14 * 1.1e-16
+
+
+def make_w(sp, w_max):
+    class WithRange:
+        pass
+
+    out = WithRange()
+    out.__dict__.update({k: getattr(sp, k) for k in (
+        "T", "omega0", "gamma_s", "omega_l", "gamma_l", "a_l", "d", "nq", "nw", "lambda_target",
+        "dispersion", "coupling", "v_l")}, q_max=1.0, w_max=w_max)
+    return out
