@@ -188,3 +188,35 @@ def make_w(sp, w_max):
         "T", "omega0", "gamma_s", "omega_l", "gamma_l", "a_l", "d", "nq", "nw", "lambda_target",
         "dispersion", "coupling", "v_l")}, q_max=1.0, w_max=w_max)
     return out
+
+
+# where a spectrum has no tables, the nodes from which tables may be taken cost
+# what they cost below (the ratio: 1 to 1.1; 1.9 to 70 when the points without a
+# table were summed in the evaluation)
+@pytest.mark.parametrize("few,many,kw", [
+    ((42, 16, 16), (43, 16, 16), dict()),
+    ((1270, 3, 1), (1300, 3, 1), dict()), ((307, 16, 16), (308, 16, 16), dict(v_l=0.3)),
+    ((307, 16, 16), (308, 16, 16), dict(coupling=1)),
+    ((9200, 3, 1), (9300, 3, 1), dict(v_l=0.3)),
+])
+def test_without_tables_as_fast_as_node_by_node(lbm, few, many, kw):
+    import time
+
+    import torch
+
+    print("time without tables", few, many, kw, flush=True)
+    sp = spectra(256, 1024, kw.get("coupling", 0), kw.get("v_l", 0.0), 1, gamma_s=0.01)
+    per_node = []
+    for nx, ny, nz in (few, many):
+        kind = (9, lbm.SLAB) if nz == 1 else (19, lbm.DUCT)
+        G = lbm.Channel(*kind, nx, ny, nz, tau=0.7, precision="f16s")
+        om = sp.omega0 * torch.linspace(0.5, 1.5, G.wall_count, dtype=torch.float64, device="cuda")
+        best = 1e9
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            G.set_friction_spectral(sp, om)
+            best = min(best, time.perf_counter() - t)
+        per_node.append(best / G.wall_count)
+    print(f"  {per_node[0] * 1e9:.1f} -> {per_node[1] * 1e9:.1f} ns per node", flush=True)
+    assert per_node[1] < 1.4 * per_node[0]
