@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "lbm_internal.h"
+#include "lbm_plan.h"
 
 using lbm::ColInfo;
 using lbm::StepArgs;
@@ -193,37 +194,20 @@ void plan_box(const std::vector<unsigned char>& fluid, Plan* P) {
     }
 }
 
-// Tiles of the two-step kernel of large channels in double.  Whole x-lines
-// where they are stored back to back, else 32 cells (whole cache lines) with a
-// halo; the range of z of a tile takes the fewest rounds of plane passes over
-// 256 CUs, of which one workgroup fills each (its first and last planes are
-// computed twice).  From 262,144 cells on: 64 x 64 x 64 13.06 -> 12.92 us,
-// all larger ones measured are faster by 3 to 40 %, 64 x 64 x 32 is slower
-// (9.4 -> 10.3).
-void plan_pair(Plan* P) {
+// Tiles of the two-step kernel of large channels in double (lbm_plan.h), from
+// 262,144 cells on (64 x 64 x 32 is slower: 9.4 -> 10.3 us).
+void plan_pair(Plan* P, bool slab) {
   Plan& pl = *P;
   if (pl.prec != LBM_F64 || pl.bouz || pl.nfluid < (1 << 18)) return;
   if (pl.ncolbox * pl.sC * (int64_t)pl.ssize >= ((int64_t)1 << 32)) return;
-  const int hx = pl.nxp <= 128 ? 0 : 1, tx = hx ? 32 : pl.nx;
-  const int rows = lbm::pair_lanes() / (tx + 2 * hx) - 2;
-  if (rows < 1) return;
-  const int xt = (pl.nxp + tx - 1) / tx, yt = (pl.ny + rows - 1) / rows;
-  const int ty = (pl.ny + yt - 1) / yt;
-  int lz = pl.nz;
-  int64_t best = INT64_MAX;
-  for (int l = 1; l <= pl.nz; l++) {
-    const int64_t n = (int64_t)xt * yt * ((pl.nz + l - 1) / l);
-    const int64_t cost = (n + 255) / 256 * (l + 2);
-    if (cost < best) {
-      best = cost;
-      lz = l;
-    }
-  }
-  for (int z0 = 0; z0 < pl.nz; z0 += lz)
-    for (int y0 = 0; y0 < pl.ny; y0 += ty)
+  const lbm::PairPlan q = lbm::choose_pair(slab, pl.nx, pl.nxp, pl.ny, pl.nz, lbm::pair_lanes());
+  if (!q.tx) return;
+  const int xt = (pl.nxp + q.tx - 1) / q.tx;
+  for (int z0 = 0; z0 < pl.nz; z0 += q.lz)
+    for (int y0 = 0; y0 < pl.ny; y0 += q.ty)
       pl.tiles.push_back(
-          lbm::BoxTile{y0, std::min(y0 + ty, pl.ny), z0, std::min(z0 + lz, pl.nz)});
-  pl.pair = lbm::PairArgs{(int)pl.tiles.size() * xt, xt, tx, hx, nullptr, nullptr};
+          lbm::BoxTile{y0, std::min(y0 + q.ty, pl.ny), z0, std::min(z0 + q.lz, pl.nz)});
+  pl.pair = lbm::PairArgs{(int)pl.tiles.size() * xt, xt, q.tx, q.hx, nullptr, nullptr};
 }
 
 lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
@@ -524,7 +508,7 @@ lbm_status make_plan(const lbm_params* p, Plan* P, std::string* err) {
 
   if (pl.Q == 19 && !pl.masked) {
     plan_box(fluid, P);
-    if (!pl.box.blocks) plan_pair(P);
+    if (!pl.box.blocks) plan_pair(P, slab);
   }
   if (pl.Q == 9 && !pl.masked) {
     // powers of two: an even number of launches in a graph, which brings the

@@ -140,3 +140,40 @@ def test_captured_steps_replay(lbm, geo, nx, ny, nz, n):
         B.step(total - B.step_count)
         assert np.array_equal(A.populations(), B.populations()), (eager, total)
     assert np.isfinite(A.flux()) and A.flux() == B.flux()
+
+
+# the pair kernel's tiles of 32 cells on x-lines that are stored back to back
+@pytest.mark.parametrize("geo,nx,ny,nz", [
+    ("duct", 96, 64, 64), ("duct", 112, 100, 60), ("duct", 103, 94, 45), ("slab", 125, 124, 25),
+    ("slab", 120, 60, 60), ("duct", 108, 51, 110),
+])
+def test_narrow_tiles_equal_single_steps(lbm, geo, nx, ny, nz):
+    print("pair, narrow tiles", geo, nx, ny, nz, flush=True)
+    compare(lbm, geo, nx, ny, nz, "f64", 1e-3 if geo == "slab" else 0.0)
+
+
+# several steps per call are at least as fast as that many calls of one step
+# (ratios of the pair kernel's former rule: 1.2 to 1.4 in graphs)
+@pytest.mark.parametrize("geo,nx,ny,nz", [
+    ("slab", 2048, 128, 1), ("slab", 1024, 128, 3), ("duct", 300, 7, 200), ("duct", 1383, 17, 17),
+    ("duct", 128, 64, 33), ("duct", 256, 128, 64),
+])
+def test_many_steps_as_fast_as_single_ones(lbm, geo, nx, ny, nz):
+    import time
+
+    import torch
+
+    print("time of steps", geo, nx, ny, nz, flush=True)
+    ch = channel(lbm, geo, nx, ny, nz, "f64")
+    best = [1e9, 1e9]
+    for _ in range(8):
+        for k, calls in enumerate((1, 128)):
+            ch.step(128)
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(calls):
+                ch.step(128 // calls)
+            torch.cuda.synchronize()
+            best[k] = min(best[k], (time.perf_counter() - t) / 128)
+    print(f"  {best[0] * 1e6:.2f} us in one call, {best[1] * 1e6:.2f} in calls of one", flush=True)
+    assert best[0] < 1.04 * best[1]
