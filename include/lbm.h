@@ -360,12 +360,16 @@ lbm_status lbm_shell_count(const lbm_ctx *ctx, size_t *n);
  * even if cached.  *bx and *us (the chosen width's step time in
  * microseconds, 0 when taken from the cache) may be NULL.  Results never
  * depend on the width: the step's arithmetic is per cell, and the
- * reductions (invariants, checked steps) keep the default blocks.
+ * reductions (invariants, checked steps) keep the default blocks.  Channels
+ * that take several steps per launch (D2Q9 slabs, small D3Q19 channels, large
+ * slabs and ducts in F64, all without noise, lines or open ends) have no width
+ * to search: *bx is the default and *us their time per step.
  * Synchronous. */
 #define LBM_TUNE_RETIME 1
 lbm_status lbm_tune(lbm_ctx *ctx, int flags, int *bx, double *us);
 /* Set the step kernel's block width directly (as lbm_tune; 0: the default,
- * min(nx rounded up to 64, 512)); LBM_EINVAL for a width not allowed.
+ * min(nx rounded up to 64, 512)); LBM_EINVAL for a width not allowed.  Single
+ * steps take it; launches of several steps have lanes of their own.
  * Synchronous. */
 lbm_status lbm_set_block(lbm_ctx *ctx, int bx);
 

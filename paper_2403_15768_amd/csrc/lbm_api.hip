@@ -1506,14 +1506,15 @@ bool block_ok(const lbm_ctx* c, int bx) {
 }
 
 // The autotuner's choices per kind of channel: lattice, storage, geometry,
-// noise form, electron lines, open ends, and size bucket (log2 of nx and of
-// the fluid columns).  Shared by every context of the process.
+// noise form, electron lines, open ends, whether a launch takes several steps,
+// and size bucket (log2 of nx and of the fluid columns).  Shared by every
+// context of the process.
 struct StepKey {
-  int Q, prec, geom, th, elec, open, nx_log2, cols_log2;
+  int Q, prec, geom, th, elec, open, several, nx_log2, cols_log2;
   bool operator<(const StepKey& o) const {
-    const int a[8] = {Q, prec, geom, th, elec, open, nx_log2, cols_log2};
-    const int b[8] = {o.Q, o.prec, o.geom, o.th, o.elec, o.open, o.nx_log2, o.cols_log2};
-    return std::lexicographical_compare(a, a + 8, b, b + 8);
+    const int a[9] = {Q, prec, geom, th, elec, open, several, nx_log2, cols_log2};
+    const int b[9] = {o.Q, o.prec, o.geom, o.th, o.elec, o.open, o.several, o.nx_log2, o.cols_log2};
+    return std::lexicographical_compare(a, a + 9, b, b + 9);
   }
 };
 std::mutex g_step_mu;
@@ -1528,19 +1529,20 @@ int log2i(int64_t v) {
   return r;
 }
 
-// Time `reps` real steps (an even number, after two untimed ones, so the
-// buffer parity comes back) with block width bx: the alternating column
-// order and the cache contents between steps are those of a run.  The steps
-// advance the state; the caller restores it from a checkpoint.
+// Time `reps` real launches (an even number, after two untimed ones, so the
+// buffer parity comes back), of one step each with block width bx or of
+// several steps where the channel takes them: the alternating column order and
+// the cache contents between launches are those of a run.  The steps advance
+// the state; the caller restores it from a checkpoint.
 lbm_status time_step_kernel(lbm_ctx* c, int bx, int reps, hipEvent_t e0, hipEvent_t e1,
                             double* us) {
-  const int saved = c->step_bx;
+  const int saved = c->step_bx, per = steps_per_launch(c);
   c->step_bx = bx;
   lbm_status s = LBM_OK;
   for (int r = 0; r < reps + 2 && s == LBM_OK; r++) {
     if (r == 2 && hipEventRecord(e0, c->stream) != hipSuccess)
       s = c->fail(LBM_EDEVICE, "hipEventRecord failed");
-    if (s == LBM_OK) s = launch_one_step(c);
+    if (s == LBM_OK) s = per > 1 ? launch_steps(c, per) : launch_one_step(c);
   }
   c->step_bx = saved;
   if (s != LBM_OK) return s;
@@ -1548,7 +1550,7 @@ lbm_status time_step_kernel(lbm_ctx* c, int bx, int reps, hipEvent_t e0, hipEven
   HIPCHK(c, hipEventSynchronize(e1));
   float ms = 0;
   HIPCHK(c, hipEventElapsedTime(&ms, e0, e1));
-  *us = 1e3 * ms / reps;
+  *us = 1e3 * ms / (reps * per);
   return LBM_OK;
 }
 
@@ -1569,7 +1571,8 @@ lbm_status lbm_set_block(lbm_ctx* c, int bx) {
 lbm_status lbm_tune(lbm_ctx* c, int flags, int* bx_out, double* us_out) {
   if (!c) return LBM_EINVAL;
   const StepKey key{c->pl.Q, c->pl.prec, c->p.geometry, c->args.th_mode, c->elec ? 1 : 0,
-                    c->args.open ? 1 : 0, log2i(c->pl.nx), log2i((int64_t)c->pl.slots.size())};
+                    c->args.open ? 1 : 0, steps_per_launch(c) > 1 ? 1 : 0, log2i(c->pl.nx),
+                    log2i((int64_t)c->pl.slots.size())};
   int pick = 0;
   double best = 0.0;
   if (!(flags & LBM_TUNE_RETIME)) {
@@ -1606,8 +1609,9 @@ lbm_status lbm_tune(lbm_ctx* c, int flags, int* bx_out, double* us_out) {
     pick = c->pl.bx;
     if ((s = time_step_kernel(c, pick, kTuneSteps, e0, e1, &best)) == LBM_OK) {
       const double keep = best * (1.0 - kTuneMargin);
+      // (launches of several steps have lanes of their own: no other width)
       for (int bx : {64, 128, 256, 512}) {
-        if (bx == c->pl.bx || !block_ok(c, bx)) continue;
+        if (bx == c->pl.bx || !block_ok(c, bx) || key.several) continue;
         double us = 0;
         if ((s = time_step_kernel(c, bx, kTuneSteps, e0, e1, &us)) != LBM_OK) break;
         if (us < keep && us < best) {
@@ -1619,7 +1623,7 @@ lbm_status lbm_tune(lbm_ctx* c, int flags, int* bx_out, double* us_out) {
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (s != LBM_OK) return s;
-    c->cur = cur0;  // every candidate took an even number of steps
+    c->cur = cur0;  // every candidate took an even number of launches
     if ((s = lbm_set_state(c, ck.data(), ck.size(), step0)) != LBM_OK) return s;
     c->checked_step = checked0;  // plain steps leave the partials alone
     std::lock_guard<std::mutex> lock(g_step_mu);
