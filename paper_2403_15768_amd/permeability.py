@@ -58,23 +58,32 @@ _AT_ONCE, _SMALL = 4, 256 << 20
 def _together(tasks, nbytes: int) -> list:
     """The results of task(stream) for every task, in their order; nbytes: the
     largest channel's footprint.  A task is done with its stream when it
-    returns."""
+    returns.  Once a task has failed none behind it is started (those that run
+    already end first), and the first failure in the tasks' order is raised."""
     import torch
 
     dev, caller = torch.cuda.current_device(), torch.cuda.current_stream()
     if nbytes > _SMALL:
         return [task(caller) for task in tasks]
 
-    def run(task):
+    failed = []  # places of the tasks that did
+
+    def run(k):
+        if failed and min(failed) < k:
+            return None
         # arenas come from the caller's stream: what may still run there on a
         # reused block comes before the task's first work on it
-        with torch.cuda.device(dev), torch.cuda.stream(caller):
-            stream = torch.cuda.Stream()
-            stream.wait_stream(caller)
-            return task(stream)
+        try:
+            with torch.cuda.device(dev), torch.cuda.stream(caller):
+                stream = torch.cuda.Stream()
+                stream.wait_stream(caller)
+                return tasks[k](stream)
+        except BaseException:
+            failed.append(k)
+            raise
 
     with ThreadPoolExecutor(_AT_ONCE) as pool:
-        return list(pool.map(run, tasks))
+        return list(pool.map(run, range(len(tasks))))
 
 
 def _tube_spec(R: int, nx: int, tau: float, g: float, precision: str) -> dict:

@@ -58,3 +58,29 @@ def test_a_failing_tube_raises(mods):
     with pytest.raises(lbm.LBMError):
         perm.sweep([3, 4], [1.0], nx=4, rel_tol=1e-12, check_every=10, max_steps=20)
     assert len(perm.sweep([3], [1.0], nx=4, rel_tol=1e-3, check_every=50)) == 1
+
+
+def test_no_tube_is_started_after_a_failure(mods):
+    # four run at a time; the fourth fails while the first three wait, so a
+    # fifth could only start after the failure
+    torch, lbm, perm = mods
+    import threading
+
+    print("sweep, tasks behind a failed one", flush=True)
+    late, ran = threading.Event(), []
+
+    def waits(stream):
+        late.wait(0.5)
+
+    def fails(stream):
+        raise ValueError("fourth")
+
+    def behind(k):
+        def task(stream):
+            ran.append(k)
+            late.set()
+        return task
+
+    with pytest.raises(ValueError, match="fourth"):
+        perm._together([waits] * 3 + [fails] + [behind(k) for k in range(8)], 0)
+    assert ran == []
