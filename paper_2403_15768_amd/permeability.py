@@ -117,7 +117,9 @@ def sweep(radii, omega_scales, spectral=None, nx: int = 16, tau: float = 0.8,
         return run
 
     points = [(R, s) for R in radii for s in (None, *omega_scales)]
-    most = max((R for R, _ in points), default=1)
+    if not points:
+        return []
+    most = max(R for R, _ in points)
     nbytes = lbm.footprint(lbm.make_params(**_tube_spec(most, nx, tau, g, precision)))
     out, q0 = [], 0.0
     for (R, s), (lam, q, n) in zip(points, _together([tube(R, s) for R, s in points], nbytes)):

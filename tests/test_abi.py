@@ -91,3 +91,10 @@ def test_masked_footprint_host_logic():
         assert lib.lbm_footprint(C.byref(q), C.byref(n)) == -1
     with pytest.raises(ValueError):
         lbm.make_params(lbm.D3Q19, lbm.MASKED, nx, ny, nz, tau=0.8, solid=np.zeros((nx, ny)))
+
+
+def test_an_empty_sweep_needs_no_gpu():
+    from paper_2403_15768_amd import permeability
+
+    assert permeability.sweep([], [1.0]) == []
+    assert permeability.sweep([], [], tau=0.1) == []  # parameters of no tube
