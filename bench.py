@@ -35,9 +35,11 @@ METRIC = "D3Q19 MLUPS + % of HBM roofline; batched solves/s and p99 time-to-stea
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_UPDATE = {"f32": 152, "f64": 304, "f16s": 76}  # 19 reads + 19 writes
 DUCT = (256, 128, 64)
+# what the counted traffic depends on: the kernels and the pair kernel's tiles
 KERNEL_SOURCES = ["paper_2403_15768_amd/csrc/lbm_device.h",
                   "paper_2403_15768_amd/csrc/lbm_kernels.hip",
-                  "paper_2403_15768_amd/csrc/lbm_pair.h"]
+                  "paper_2403_15768_amd/csrc/lbm_pair.h",
+                  "paper_2403_15768_amd/csrc/lbm_plan.h"]
 # counter-measured HBM bytes per step of the dominant kernel, per workload
 # and storage (no noise, periodic ends); used while the kernel sources match
 COUNTERS = {
@@ -57,6 +59,14 @@ def kernel_hash() -> str:
         with open(os.path.join(ROOT, p), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def step_bytes(precision: str, pair: bool) -> int:
+    """Bytes per cell and step that the step kernel cannot do without: each
+    population read once and written once per launch, which takes two steps
+    where the pair kernel runs (the 256 x 128 x 64 duct and slab in double
+    without noise, lines or open ends)."""
+    return BYTES_PER_UPDATE[precision] // (2 if pair else 1)
 
 
 def log(*a):
@@ -183,7 +193,8 @@ def extras(torch, lbm, inputs, args):
     cells = ch.fluid_count
     out["duct_f64"] = {"mlups": round(cells * 2000 / wall / 1e6, 1),
                        "kernel_us": round(kms * 1e3 / 2000, 2),
-                       "hbm_frac": round(304 * cells / (kms * 1e-3 / 2000) / 1e9 / HBM_PEAK_GBS, 4)}
+                       "hbm_frac": round(step_bytes("f64", True) * cells / (kms * 1e-3 / 2000)
+                                         / 1e9 / HBM_PEAK_GBS, 4)}
     ch.close()
     del ch
     # the duct far beyond the 256 MB last-level cache (512 x 256 x 128: 2.55
@@ -703,7 +714,9 @@ def main():
 
     mlups = cells * args.steps / wall / 1e6
     kern_s = kernel_ms * 1e-3 / args.steps
-    bpu = BYTES_PER_UPDATE[args.precision]
+    pair = (args.precision == "f64" and not corr and not args.thermal and not args.open_ends
+            and not (slab and args.electrons))
+    bpu = step_bytes(args.precision, pair)
     achieved = bpu * cells / kern_s / 1e9
     log(f"bench: {mlups:.1f} MLUPS, step kernel {kern_s * 1e6:.2f} us, {achieved:.0f} GB/s")
 
@@ -716,7 +729,7 @@ def main():
 
     # the same footprint as one step (a population buffer read, the other
     # written; partly held by the 256 MB last-level cache), and a 1 GiB copy
-    copy_gbs = copy_ceiling(torch, lbm, bpu // 2 * cells)
+    copy_gbs = copy_ceiling(torch, lbm, BYTES_PER_UPDATE[args.precision] // 2 * cells)
     copy_big = copy_ceiling(torch, lbm, 1 << 30)
     log(f"bench: copy ceiling {copy_gbs:.0f} GB/s (same footprint), {copy_big:.0f} GB/s (1 GiB)")
     ext = {} if args.no_extras else extras(torch, lbm, inputs, args)
@@ -774,9 +787,8 @@ def main():
                      "traffic": traffic,
                      "traffic_GBs": None if traffic is None else round(traffic / kern_s / 1e9, 1),
                      "kernel": ("k_step_masked<D3Q19>" if corr else
-                                "k_step_pair (two steps per launch; bytes of two single steps)"
-                                if args.precision == "f64" and not args.thermal
-                                and not args.open_ends and not (slab and args.electrons) else
+                                "k_step_pair (two steps per launch, each population read "
+                                "and written once)" if pair else
                                 "k_step<D3Q19>" if not args.thermal else
                                 f"k_step<D3Q19, noise {args.thermal}>")
                                + (", k_step_lines with the sheets" if slab and args.electrons else "")

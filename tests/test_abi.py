@@ -98,3 +98,13 @@ def test_an_empty_sweep_needs_no_gpu():
 
     assert permeability.sweep([], [1.0]) == []
     assert permeability.sweep([], [], tau=0.1) == []  # parameters of no tube
+
+
+def test_bench_prices_the_pair_kernel_by_what_it_moves():
+    # one read and one write of 19 doubles per cell for two steps
+    import bench
+
+    assert bench.step_bytes("f64", True) == 152 and bench.step_bytes("f64", False) == 304
+    assert bench.step_bytes("f32", False) == 152 and bench.step_bytes("f16s", False) == 76
+    assert all(os.path.exists(os.path.join(ROOT, p)) for p in bench.KERNEL_SOURCES)
+    assert "lbm_plan.h" in " ".join(bench.KERNEL_SOURCES)  # the tiles decide the traffic
