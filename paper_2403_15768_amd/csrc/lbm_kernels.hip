@@ -54,10 +54,12 @@ __device__ __forceinline__ void step_cell(const S* __restrict__ src, S* __restri
   if constexpr (TH != 0)
     thermal_noise<L, M, TH, NormalT<S>>(a, (uint32_t)col * (uint32_t)a.nx + (uint32_t)x, step, xi);
   // open ends: the ghosts' values, in flight with the gather in float storage
-  // (256 x 128 x 64 duct 63.4 -> 58.6 us, smaller ones by 5 to 10 %); in double
-  // and on tubes the registers they hold cost more (115.9 -> 117.4, tube 45.3
-  // -> 46.8)
-  constexpr bool kEarly = OPEN && !BOUZ && sizeof(S) == 4;
+  // (256 x 128 x 64 duct 63.4 -> 58.6 us, smaller ones by 5 to 10 %) and on
+  // D2Q9 in double (323 x 44 4.03 -> 3.90, which loading them after the gather
+  // had made slower: 3.91 when the reading step formed them); in D3Q19 in
+  // double and on tubes the registers they hold cost more (115.9 -> 117.4, tube
+  // 45.3 -> 46.8)
+  constexpr bool kEarly = OPEN && !BOUZ && (sizeof(S) == 4 || (L::Q == 9 && sizeof(S) == 8));
   M sh[kEndSlots];
   if constexpr (kEarly) open_load<L, M>(a, a.bmom, col, xc, sh);
   gather<L, S, M, M, BOUZ, ELEC, OPEN>(src, a, col, xc, info, df);
