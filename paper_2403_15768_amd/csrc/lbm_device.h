@@ -247,7 +247,10 @@ struct WorkItem {
 // and every population access is (uniform line base) + (32-bit lane index).
 // The byte offset is formed in 32-bit unsigned arithmetic so that the
 // compiler can address with a scalar base and a 32-bit vector offset instead
-// of one 64-bit vector address per access (x < nxp <= 2^24: no wrap).
+// of one 64-bit vector address per access.  It must not reach 2^32: x < nxp <=
+// 2^24 within an x-line; k_step_box and k_step_pair index whole population
+// buffers, which their plans keep below 4 GiB (their element offsets may wrap
+// on the way, modulo 2^32 as the sum does).
 #define LBM_GLOBAL __attribute__((address_space(1)))
 template <typename T>
 __device__ __forceinline__ const LBM_GLOBAL T* gbl(const T* p) {

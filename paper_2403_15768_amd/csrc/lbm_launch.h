@@ -82,8 +82,9 @@ hipError_t launch_step_lines(int q, int prec, const void* src, void* dst, const 
                              hipStream_t st);
 // (src, dst, StepArgs, e_src, e_dst, ue, ElecArgs)
 const void* lines_kernel_ptr(int q, int prec, int th_mode);
-// open x ends: the moments of the first and last node of every column of
-// src ([side][column][4] doubles), before the step that reads src
+// open x ends: the records of the ghosts beside the first and the last node of
+// every column of src ([side][column][kEndSlots] doubles, see end_shifts),
+// before the step that reads src
 hipError_t launch_open_moments(int q, int prec, const void* src, const StepArgs& a, double* bmom,
                                hipStream_t st);
 const void* open_moments_kernel_ptr(int q, int prec);  // (src, StepArgs, bmom)
@@ -94,10 +95,13 @@ hipError_t launch_moments(int q, int prec, const void* src, const StepArgs& a, b
 // memory, device pointer) receives the same if not null
 hipError_t launch_reduce_final(const double* partials, int64_t nblocks, double* out, int nx,
                                double mass0, hipStream_t st, double* out_host = nullptr);
-// the friction quadrature; scratch (device, at least 18 n bytes) holds the
-// tables of the piecewise sums, which take over from the node-by-node sums
-// at kQuadSharedNodes nodes (spectra whose omega sum does not depend on q) or
-// kQuadTableNodes (the others).  The result does not depend on its size.
+// the friction quadrature; scratch (device) holds the tables of the piecewise
+// sums, which take over from the node-by-node sums at kQuadSharedNodes nodes
+// (spectra whose omega sum does not depend on q) or kQuadTableNodes (the
+// others).  It needs 1 KiB and one table of 40 KiB, or a group of eight and a
+// bit per q point: less than 18 bytes per node from there on, which a context's
+// population buffer always has (up to 20,480 q points; above, from the node
+// count that gives as much).  The result does not depend on its size.
 constexpr int64_t kQuadSharedNodes = 2560, kQuadTableNodes = 18432;
 hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, double* raw,
                            double* lambda, void* scratch, int64_t scratch_bytes, hipStream_t st);

@@ -32,8 +32,9 @@ namespace lbm {
 // plane are in flight while the second step computes.
 //
 // Measured per step: 256 x 128 x 64 108.4 -> 82.2 us, 320 x 128 x 64 137.1 ->
-// 97.9, 200 x 100 x 60 69.8 -> 57.2, 64 x 128 x 64 24.5 -> 19.5, 40 x 120 x 60
-// 15.5 -> 13.9.  What bounds it now is latency with two waves per SIMD (VALU
+// 97.9, 200 x 100 x 60 69.8 -> 57.2, 64 x 128 x 64 24.5 -> 19.2, 40 x 120 x 60
+// 15.5 -> 13.8 (lbm_plan.h: the tiles, and the channels that keep single steps).
+// What bounds it now is latency with two waves per SIMD (VALU
 // busy for a quarter of the time).  Float storage was slower this way (53 ->
 // 79 us: its arithmetic is double too, and its rounding adds to it), half
 // storage (28 -> 44 us) and interpolated walls (95 -> 107 us) as well.
