@@ -99,9 +99,9 @@ hipError_t launch_reduce_final(const double* partials, int64_t nblocks, double* 
 // sums, which take over from the node-by-node sums at kQuadSharedNodes nodes
 // (spectra whose omega sum does not depend on q) or kQuadTableNodes (the
 // others).  It needs 1 KiB and one table of 40 KiB, or a group of eight and a
-// bit per q point: less than 18 bytes per node from there on, which a context's
-// population buffer always has (up to 20,480 q points; above, from the node
-// count that gives as much).  The result does not depend on its size.
+// byte per q point: less than 18 bytes per node from there on, which a
+// context's population buffer always has (up to 2560 q points; with more, from
+// the node count that gives as much).  The result does not depend on its size.
 constexpr int64_t kQuadSharedNodes = 2560, kQuadTableNodes = 18432;
 hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, double* raw,
                            double* lambda, void* scratch, int64_t scratch_bytes, hipStream_t st);

@@ -332,13 +332,8 @@ __device__ __forceinline__ double omega_sum(const OmegaTerm& t, double P, double
 // frequency must not spoil the other nodes' tables)
 __global__ void __launch_bounds__(kQuadThreads) k_quad_range(const double* __restrict__ omega,
                                                              int64_t n,
-                                                             double* __restrict__ range,
-                                                             uint32_t* __restrict__ over,
-                                                             int words) {
+                                                             double* __restrict__ range) {
   __shared__ double red[2][kQuadThreads / 64];
-  for (int w = (int)blockIdx.x * kQuadThreads + threadIdx.x; w < words;
-       w += kRangeBlocks * kQuadThreads)
-    over[w] = 0u;  // no q without a table yet
   double lo = INFINITY, hi = 0.0;
   for (int64_t k = (int64_t)blockIdx.x * kQuadThreads + threadIdx.x; k < n;
        k += (int64_t)kRangeBlocks * kQuadThreads) {
@@ -369,11 +364,11 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_range(const double* __res
 }
 
 // one block per table: the panel width from the poles' distance to the range;
-// a q whose table would be too long gets its bit in `over`
+// over (not shared): which q's table would be too long
 __global__ void __launch_bounds__(kQuadThreads) k_quad_plan(SpecArgs s, int shared, int a0,
                                                             const double* __restrict__ range,
                                                             TabInfo* __restrict__ info,
-                                                            uint32_t* __restrict__ over) {
+                                                            uint8_t* __restrict__ over) {
   __shared__ double red[kQuadThreads / 64];
   double lo = s.omega0, hi = s.omega0;
   for (int b = 0; b < kRangeBlocks; b++) {
@@ -411,7 +406,7 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_plan(SpecArgs s, int shar
     t.s_lo = range_s > 0.0 ? s_lo : s_lo - 0.5 * t.h;
     t.pad = 0;
     info[blockIdx.x] = t;
-    if (t.np > kTabCap && !shared) atomicOr(&over[a >> 5], 1u << (a & 31));
+    if (!shared) over[a] = t.np > kTabCap;
   }
 }
 
@@ -595,15 +590,14 @@ struct RestEntry {
 template <bool SCREEN>
 __global__ void __launch_bounds__(kQuadThreads)
     k_quad_rest(SpecArgs s, const double* __restrict__ omega, int64_t n,
-                const uint32_t* __restrict__ over, double* __restrict__ raw) {
+                const uint8_t* __restrict__ over, double* __restrict__ raw) {
   __shared__ RestEntry tab[kRestTile];
   __shared__ double red[kRestNodes][kQuadThreads / 64];
   __shared__ int pick[64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int words = (s.nq + 31) / 32;
-  uint32_t any = 0;
-  for (int w = 0; w < words; w++) any |= over[w];
-  if (!any) return;
+  int any = 0;
+  for (int a = tid; a < s.nq; a += kQuadThreads) any |= over[a];
+  if (!__syncthreads_or(any)) return;
   const double dq = s.q_max / s.nq, dw = s.w_max / s.nw;
   bool built = false;
   for (int64_t k0 = (int64_t)blockIdx.x * kRestNodes; k0 <= n;
@@ -635,8 +629,8 @@ __global__ void __launch_bounds__(kQuadThreads)
       }
       for (int a0 = 0; a0 < s.nq; a0 += 64) {
         // the word's points, one after the other in pick
-        uint64_t word = over[a0 >> 5];
-        if ((a0 >> 5) + 1 < words) word |= (uint64_t)over[(a0 >> 5) + 1] << 32;
+        const uint64_t word =
+            __builtin_amdgcn_ballot_w64(a0 + lane < s.nq && over[a0 + lane] != 0);
         const int m = __popcll(word);
         if (m == 0) continue;
         __syncthreads();
@@ -794,25 +788,25 @@ static bool quad_shared(const SpecArgs& s) { return !s.coupling && s.v_l == 0.0;
 static constexpr int64_t kGroupBytes = kTabGroup * (kTabDoubles * 8 + (int64_t)sizeof(TabInfo));
 static constexpr int64_t kRangeBytes = kRangeBlocks * 2 * 8;
 static constexpr int64_t kSharedBytes = kTabDoubles * 8 + (int64_t)sizeof(TabInfo);
-// a bit for every q without a table (not shared), in whole words for the
-// tables' alignment
-static int64_t over_bytes(const SpecArgs& s) { return ((int64_t)s.nq + 63) / 64 * 8; }
+// whether each q has a table (not shared), in whole words for the tables'
+// alignment
+static int64_t over_bytes(const SpecArgs& s) { return ((int64_t)s.nq + 7) / 8 * 8; }
 static_assert(18 * kQuadSharedNodes >= kRangeBytes + kSharedBytes, "scratch");
-static_assert(18 * kQuadTableNodes >= kRangeBytes + kGroupBytes + 20480 / 8, "scratch");
+static_assert(18 * kQuadTableNodes >= kRangeBytes + kGroupBytes + 2560, "scratch");
 static constexpr int kMinRows = 4;
 
 hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, double* raw,
                            double* lambda, void* scratch, int64_t scratch_bytes, hipStream_t st) {
   const bool shared = quad_shared(s);
   const int64_t mask = shared ? 0 : over_bytes(s);
-  // (above 20,480 q points the mask may need more nodes than the rule asks for)
+  // (above 2560 q points their bytes may need some more nodes: 4096 from 18,503)
   if (n >= (shared ? kQuadSharedNodes : kQuadTableNodes) &&
       std::min(18 * n, scratch_bytes) >=
           kRangeBytes + mask + (shared ? kSharedBytes : kGroupBytes)) {
     char* p = static_cast<char*>(scratch);
     double* range = reinterpret_cast<double*>(p);
     p += kRangeBytes;
-    uint32_t* over = reinterpret_cast<uint32_t*>(p);
+    uint8_t* over = reinterpret_cast<uint8_t*>(p);
     p += mask;
     const int64_t left = scratch_bytes - kRangeBytes - mask - (shared ? kSharedBytes : 0);
     const int64_t row = 8 * (n + 1), each = shared ? 0 : kGroupBytes;
@@ -829,7 +823,7 @@ hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, do
     const unsigned nblk = (unsigned)((n + 1 + kQuadThreads - 1) / kQuadThreads);
     constexpr unsigned kBuildX = (kTabCap + kBuildPanels - 1) / kBuildPanels;
     hipLaunchKernelGGL(k_quad_range, dim3(kRangeBlocks), dim3(kQuadThreads), 0, st, omega, n,
-                       range, over, (int)(mask / 4));
+                       range);
     for (int g0 = 0; g0 < total; g0 += fit) {
       const int g = std::min(fit, total - g0);
       const int tables = shared ? 1 : std::min(g * kTabGroup, s.nq - g0 * kTabGroup);
