@@ -220,3 +220,39 @@ def test_without_tables_as_fast_as_node_by_node(lbm, few, many, kw):
         per_node.append(best / G.wall_count)
     print(f"  {per_node[0] * 1e9:.1f} -> {per_node[1] * 1e9:.1f} ns per node", flush=True)
     assert per_node[1] < 1.4 * per_node[0]
+
+
+# the same without tables: a bad frequency spoils its own node only, and the
+# static call replays in a graph
+@pytest.mark.parametrize("coupling,n", [(0, 5000), (1, 20000)])
+def test_without_tables_bad_frequency_and_graph(lbm, coupling, n):
+    import torch
+
+    print("without tables", coupling, n, flush=True)
+    sp = spectra(70, 64, coupling, 0.0, 1, gamma_s=0.002)
+    om = sp.omega0 * np.random.default_rng(5).uniform(0.5, 1.5, n)
+    om[:2] = sp.omega0 * 0.5, sp.omega0 * 1.5  # the range stays
+    clean = static(lbm, sp, om)
+    assert np.all(np.isfinite(clean)) and np.all(clean > 0)
+    bad = om.copy()
+    bad[[7, 4000]] = np.nan, np.inf
+    got = static(lbm, sp, bad)
+    rest = np.ones(n, bool)
+    rest[[7, 4000]] = False
+    assert np.all(np.isnan(got[~rest])) and np.array_equal(got[rest], clean[rest])
+    s = lbm.make_spectral(sp)
+    d_om = torch.tensor(om, dtype=torch.float64, device="cuda")
+    d_lam = torch.zeros(n, dtype=torch.float64, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rc = lbm.load().lbm_friction_quadrature_static(
+            C.byref(s), C.c_void_p(d_om.data_ptr()), n, C.c_void_p(d_lam.data_ptr()),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    for _ in range(3):
+        d_lam.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(d_lam.cpu().numpy(), clean)
+        static(lbm, spectra(32, 64, 1 - coupling, 0.0, 1), om[::-1].copy())
