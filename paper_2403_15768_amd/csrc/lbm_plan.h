@@ -15,8 +15,10 @@ struct PairPlan {
 
 // Times in us by a model fitted to 300 measurements of 220 channels, 1 to 32768
 // cells long and of one to 512 rows and planes (6 % rms): channels in double of
-// at least 2^18 cells, 256 CUs.  `far`: the share of the state (both buffers,
-// mb in MB) that the 256 MB last-level cache no longer keeps.
+// at least 2^18 cells, 256 CUs.  On 110 other channels its choice was slower
+// than single steps once (4 %) and missed 4 to 10 % three times.  `far`: the
+// share of the state (both buffers, mb in MB) that the 256 MB last-level cache
+// no longer keeps.
 inline double pair_far(double mb) { return std::min(1.0, std::max(0.0, (mb - 255.0) / 35.0)); }
 
 // One step per launch: by the cells, padding included, and by the columns and
@@ -26,7 +28,7 @@ inline double single_step_us(int nx, int nxp, int ny, int nz) {
   const double cols = (double)ny * nz, far = pair_far(cols * nxp * 304e-6);
   const double per_cell = nx <= 128 && nx % 8 ? 0.0487 : 0.0462;
   const double near_line =
-      std::max({per_cell * nxp, 1.0 + 0.027 * nxp, 1.8 * ((nx + 63) / 64)});
+      std::max({per_cell * nxp, 1.0 + 0.027 * nxp, 1.95 * ((nx + 63) / 64)});
   const double far_line = std::max(near_line, (nx < 400 ? 0.052 : 0.057) * nxp);
   return 1.3 + 1e-3 * cols * ((1.0 - far) * near_line + far * far_line);
 }
@@ -41,8 +43,9 @@ inline double pair_steps_us(bool slab, int nxp, int ny, int nz, const PairPlan& 
   const double each = (double)tiles / rounds;  // tiles of a round
   const int zt = (nz + p.lz - 1) / p.lz;
   const double passes = rounds * (p.lz + 2 - (slab || zt > 2 ? 0.0 : 0.7 / zt));
-  const double near_pass = (rounds > 1 ? 4.15 : 3.0 + 1.5 * std::min(1.0, each / 200.0) + 0.2 * p.hx) +
-                           (p.ty >= ny ? 0.3 : 0.0);
+  const double one_round =
+      (slab ? 2.9 : 3.0) + 1.5 * std::min(1.0, each / 200.0) + (p.hx ? 0.2 : 0.0);
+  const double near_pass = (rounds > 1 ? 4.15 : one_round) + (p.ty >= ny ? 0.3 : 0.0);
   const double stored = 1e-3 * std::max(each, 224.0) * p.tx * p.ty * p.lz / (p.lz + 2);
   const double far_pass = std::max(near_pass, (p.hx ? 2.5 : 2.1) + 0.045 * stored);
   const double far = pair_far((double)ny * nz * nxp * 304e-6);
