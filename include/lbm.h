@@ -196,9 +196,9 @@ lbm_status lbm_set_friction_spectral(lbm_ctx *ctx, const lbm_spectral *sp,
  * hip_stream: a hipStream_t (NULL = default stream); asynchronous, no
  * synchronisation, no allocation, no memset, so it may be captured.  The raw
  * quadrature sums and its tables live in a fixed device array of
- * LBM_STATIC_MAX_NODES + 1 doubles and 16 MiB (24 MiB) per GPU, held until the process ends and shared by every
- * call on that GPU: calls that overlap on one GPU (on different streams
- * without ordering) race.  n > LBM_STATIC_MAX_NODES or invalid spectral
+ * LBM_STATIC_MAX_NODES + 1 doubles and 16 MiB (24 MiB) per GPU, held until the
+ * process ends and shared by every call on that GPU: calls that overlap on one
+ * GPU (on different streams without ordering) race.  n > LBM_STATIC_MAX_NODES or invalid spectral
  * parameters -> LBM_EINVAL; a failed launch -> LBM_EDEVICE. */
 #define LBM_STATIC_MAX_NODES ((size_t)1 << 20)
 lbm_status lbm_friction_quadrature_static(const lbm_spectral *sp, const double *omega, size_t n,
@@ -373,7 +373,8 @@ lbm_status lbm_tune(lbm_ctx *ctx, int flags, int *bx, double *us);
  * Synchronous. */
 lbm_status lbm_set_block(lbm_ctx *ctx, int bx);
 
-/* Advance nsteps >= 0 time steps (asynchronous).  One step is the LB update
+/* Advance nsteps >= 0 time steps (asynchronous; the buffers swap once per
+ * launch, which may take several steps).  One step is the LB update
  * of Sec. 4 for the water: pull streaming, the wall rule at the liquid/solid
  * links (Sec. 4.2; Navier-slip friction of Eq. 5 / Eq. 27), BGK collision
  * with the bulk force of Eq. 2 as a Guo source; plus the species and noise
