@@ -261,8 +261,12 @@ __global__ void __launch_bounds__(kQuadThreads) k_friction_full(SpecArgs s,
 // Work: 129,024 nodes x 256 q x 20 multiply-adds and a table of up to 256 x
 // 256 panels x 20 points x 1024 omegas, instead of 129,024 x 262,144 points.
 // Measured (whole lbm_set_friction_spectral and lbm_get_friction): the R = 32
-// tube's 129,024 nodes 10.9 -> 0.43 ms, screened 32,256 nodes 5.8 -> 0.30 ms;
-// relative error against 64 bits unchanged (3e-16 to 4e-16).
+// tube's 129,024 nodes 10.9 -> 0.44 ms, screened 31,744 nodes 5.8 -> 0.30 ms.
+// Root mean square error of lambda against long double sums, ten spectra: plain
+// 4.1e-16 node by node, 2.6e-16 so; screened 3.1e-16 and 2.4e-16.  The groups of q
+// are added from the last to the first: the many beyond the peak of q^3 e^{-2qd}
+// while the sum is still small (from the first to the last, each of them
+// rounded the whole sum: 3.2e-16 and 5.0e-16).
 //
 // A table that would need more than kTabCap panels (poles close to the real
 // axis, or a wide range of Omega) is not built: its q is summed node by node
@@ -490,9 +494,10 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_build(SpecArgs s, int sha
 // One wall node per lane: the sums of q^3 e^{-2qd} P F_q over groups of
 // kTabGroup q points.  The q's table sits in LDS, coefficient by coefficient
 // (neighbouring nodes have nearly the same Omega, so the panels of a wave are
-// few and next to each other: the same place or different banks).  With part, block row y takes `per` groups and leaves the sum of
-// each in its row of part; without, one block adds all `groups` of them to
-// raw in order, as k_quad_sum adds rows.
+// few and next to each other: the same place or different banks).  With part,
+// block row y takes `per` groups and leaves the sum of each in its row of part;
+// without, one block adds all `groups` of them to raw, the last one first, as
+// k_quad_sum adds rows.
 __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shared, int g0,
                                                             int groups, int per,
                                                             const double* __restrict__ omega,
@@ -507,10 +512,12 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shar
   const int tid = threadIdx.x;
   const int64_t k = (int64_t)blockIdx.x * kQuadThreads + tid;
   const double om = fabs(k < n ? omega[k] : s.omega0);  // k >= n: reference or padding
-  double sum = !part && g0 > 0 && k <= n ? raw[k] : 0.0;
+  const bool first = (g0 + groups) * kTabGroup >= s.nq;
+  double sum = !part && !first && k <= n ? raw[k] : 0.0;
   for (int gi = 0; gi < per; gi++) {
-    const int gl = (int)blockIdx.y * per + gi;  // the group within this launch's tables
-    if (gl >= groups) break;
+    // the group within this launch's tables
+    const int gl = part ? (int)blockIdx.y * per + gi : groups - 1 - gi;
+    if (gl >= groups || gl < 0) break;
     const int ga = (g0 + gl) * kTabGroup;        // its first q point
     const int na = min(kTabGroup, s.nq - ga);
     __syncthreads();
@@ -551,12 +558,11 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_eval(SpecArgs s, int shar
     sum += acc;
     if (part && k <= n) part[(int64_t)gl * (n + 1) + k] = acc;
   }
-  if (!part && k <= n)
-    raw[k] = g0 + groups >= (s.nq + kTabGroup - 1) / kTabGroup ? quad_scale(s) * sum : sum;
+  if (!part && k <= n) raw[k] = g0 == 0 ? quad_scale(s) * sum : sum;
 }
 
-// raw[k]: the groups' partial sums in group order (over several calls where
-// the scratch holds fewer groups than there are)
+// raw[k]: the groups' partial sums, the last group first (over several calls
+// where the scratch holds fewer groups than there are)
 __global__ void __launch_bounds__(kQuadThreads) k_quad_sum(SpecArgs s, int shared, int first,
                                                            int last, int groups,
                                                            const TabInfo* __restrict__ info,
@@ -565,7 +571,7 @@ __global__ void __launch_bounds__(kQuadThreads) k_quad_sum(SpecArgs s, int share
   const int64_t k = (int64_t)blockIdx.x * kQuadThreads + threadIdx.x;
   if (k > n || (shared && info[0].np > kTabCap)) return;
   double t = first ? 0.0 : raw[k];
-  for (int g = 0; g < groups; g++) t += part[(int64_t)g * (n + 1) + k];
+  for (int g = groups - 1; g >= 0; g--) t += part[(int64_t)g * (n + 1) + k];
   raw[k] = last ? quad_scale(s) * t : t;
 }
 
@@ -824,10 +830,10 @@ hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, do
     constexpr unsigned kBuildX = (kTabCap + kBuildPanels - 1) / kBuildPanels;
     hipLaunchKernelGGL(k_quad_range, dim3(kRangeBlocks), dim3(kQuadThreads), 0, st, omega, n,
                        range);
-    for (int g0 = 0; g0 < total; g0 += fit) {
-      const int g = std::min(fit, total - g0);
+    for (int end = total; end > 0; end -= fit) {
+      const int g = std::min(fit, end), g0 = end - g;
       const int tables = shared ? 1 : std::min(g * kTabGroup, s.nq - g0 * kTabGroup);
-      if (!shared || g0 == 0) {
+      if (!shared || end == total) {
         hipLaunchKernelGGL(k_quad_plan, dim3((unsigned)tables), dim3(kQuadThreads), 0, st, s,
                            shared ? 1 : 0, g0 * kTabGroup, range, info, over);
         hipLaunchKernelGGL(k_quad_build, dim3(kBuildX, (unsigned)tables), dim3(kQuadThreads), 0,
@@ -842,7 +848,7 @@ hipError_t launch_friction(const SpecArgs& s, const double* omega, int64_t n, do
                          omega, n, info, tab, part, raw);
       if (rows)
         hipLaunchKernelGGL(k_quad_sum, dim3(nblk), dim3(kQuadThreads), 0, st, s, shared ? 1 : 0,
-                           g0 == 0 ? 1 : 0, g0 + g == total ? 1 : 0, g, info, part, n, raw);
+                           end == total ? 1 : 0, g0 == 0 ? 1 : 0, g, info, part, n, raw);
     }
     // What has no table, node by node.  Some thousand blocks: with nothing to do
     // (the usual case) they are gone in 2 us, and as few as are resident were 9 %

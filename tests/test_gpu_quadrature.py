@@ -256,3 +256,24 @@ def test_without_tables_bad_frequency_and_graph(lbm, coupling, n):
         torch.cuda.synchronize()
         assert np.array_equal(d_lam.cpu().numpy(), clean)
         static(lbm, spectra(32, 64, 1 - coupling, 0.0, 1), om[::-1].copy())
+
+
+# no less precise than the sums node by node: the root mean square error of
+# lambda over nodes and spectra, both against long double sums (1.6 times theirs
+# when the groups of q were added in ascending order)
+@pytest.mark.parametrize("coupling,v_l", [(0, 0.0), (1, 0.3)])
+def test_as_precise_as_node_by_node(lbm, coupling, v_l):
+    print("precision", coupling, v_l, flush=True)
+    err = {40: [], 310: []}  # 2400 nodes: node by node; 18600: tables
+    for seed in range(6):
+        sp = inputs.draw_spectral(np.random.default_rng([seed, 1]))
+        sp.coupling, sp.v_l, sp.dispersion = coupling, v_l, 1
+        om = sp.omega0 * np.random.default_rng([seed, 2]).uniform(0.55, 1.45, 60 * 310)
+        _, want = oracle.friction(oracle_spectra(sp), om[:12], kind="f80")
+        for nx, e in err.items():
+            G = lbm.Channel(19, lbm.DUCT, nx, 16, 16, tau=0.7)
+            G.set_friction_spectral(sp, om[: G.wall_count])
+            e += list(G.get_friction()[:12] / want - 1)
+    rms = {nx: float(np.sqrt(np.mean(np.square(e)))) for nx, e in err.items()}
+    print(f"  node by node {rms[40]:.2e}, tables {rms[310]:.2e}", flush=True)
+    assert rms[310] < 1.2 * rms[40]
