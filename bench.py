@@ -792,8 +792,7 @@ def main():
                                 "k_step<D3Q19>" if not args.thermal else
                                 f"k_step<D3Q19, noise {args.thermal}>")
                                + (", k_step_lines with the sheets" if slab and args.electrons else "")
-                               + (" + k_open_ends (time per step covers both)"
-                                  if args.open_ends else ""),
+                               + (", open ends" if args.open_ends else ""),
                      "kernel_us": round(kern_s * 1e6, 3), "bytes_per_update": bpu},
         "cpu_baseline": cpu,
         "extras": ext,
